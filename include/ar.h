@@ -115,12 +115,8 @@ typedef enum { AR_SUM = 0, AR_MAX = 1 } ar_op;
  *                                   default: the size rules given there),
  *                                   its chunks ordered by the default rule
  *                                   (1: one contiguous region of each slice
- *                                   per XCD on flat columns above 16 MiB per
- *                                   rank, on blocks that all start on the
- *                                   4 KB chunk grid for P >= 104 or from
- *                                   32 MiB per rank, and on other blocks
- *                                   for P >= 104 below 256 MiB per rank;
- *                                   else interleaved over the XCDs), always
+ *                                   per XCD above 16 MiB per rank, else
+ *                                   interleaved over the XCDs), always
  *                                   interleaved (2), or always in regions
  *                                   (3);
  *   AR_FUSED_PACKED = 0|1           column launches other than the latency-
@@ -204,12 +200,11 @@ typedef struct {
                                         destination -- flat columns (short blocks), or
                                         blocks of at least 1024 elements in rank buffers
                                         of at least 2 MiB (AR_BCAST_STREAM overrides the
-                                        size rule) -- for calls whose
-                                        instances are contiguous (batch 1 or
-                                        instance_stride = n) in 16-byte aligned rank
-                                        buffers, with batch * n below 2^32 - 1024; other
-                                        calls, and 0 here, take the tiled broadcast (the
-                                        same bits)                                        */
+                                        size rule), for rank buffers of any alignment
+                                        and instances with or without gaps whose span,
+                                        (batch - 1) * instance_stride + n, is below
+                                        2^32 - 2048 elements; other calls, and 0 here,
+                                        take the tiled broadcast (the same bits)          */
 } ar_stats;
 
 /* One launch of the STEPWISE path: a list of placement ranges.  In a range,

@@ -162,7 +162,7 @@ struct ColArgs {
   uint32_t total_tiles;     // batch * P * tiles (< 2^31)
   FastDiv tiles, pdiv;      // column tiles per block, P
   int32_t P, r;             // r: distribution steps removed (kept shifts w = min(2^r, P))
-  int32_t split;            // 1: store the block's result to its root rank only (a broadcast follows)
+  int32_t split;            // 1: store the result to rank 0 only (a broadcast follows)
   uint32_t lds;             // as in FusedArgs
   // Latency-optimal plans (r = L): the tree of every rank is the same for
   // every block, so the kernels may tile the batch * n columns as one flat
@@ -183,6 +183,12 @@ struct ColArgs {
   // each lane from its index i in the instance): the first m blocks hold
   // q + 1 elements (q1div = q + 1), the others q (qdiv = max(q, 1)).
   FastDiv q1div, qdiv;
+  // The call's extent, and the broadcast of a split call: copied destination
+  // by destination (dest_major) in XCD regions or interleaved, with
+  // nontemporal stores or not, on a device of `xcds` XCDs.
+  int64_t n, instances;
+  uint32_t xcds;
+  int32_t dest_major, bcast_regions, bcast_nt;
 };
 
 // dtype: 0 int32, 1 float32; op: 0 sum, 1 max.  Returns a hipError_t value.
@@ -212,16 +218,17 @@ int launch_fused_rot_any(const ColArgs& a, int P, int dtype, int op, bool ring, 
 // power of two and any r, and the Ring for any P in 2..128.
 int launch_fused_xor(const ColArgs& a, int P, int dtype, int op, bool nt, int grid, void* stream);
 int launch_fused_ring(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream);
-// Second half of a split fused launch (broadcast.hip): block b's result,
-// stored on rank b by the reducing kernel, copied to the other P - 1 ranks.
+// Second half of a split fused launch (broadcast.hip): the results, stored
+// on rank 0 by the reducing kernel, copied to the other P - 1 ranks.
 int launch_broadcast(const ColArgs& a, int dtype, bool nt, int grid, void* stream);
 
 // The same copy ordered destination by destination (broadcast.hip), for
-// contiguous instances in 16-byte aligned rank buffers.  A workgroup copies
-// one chunk of kStreamChunk consecutive columns of the batch's flat column
-// space (the byte offset in every rank buffer is 4 * column) to one
-// destination rank, one 16-byte store per thread; ids run slice by slice
-// (C chunks per slice), destination by destination, chunk by chunk.
+// contiguous instances in 16-byte aligned rank buffers (launch_broadcast
+// does the same for other layouts).  A workgroup copies one chunk of
+// kStreamChunk consecutive columns of the batch's flat column space (the
+// byte offset in every rank buffer is 4 * column) to one destination rank,
+// one 16-byte store per thread; ids run slice by slice (C chunks per slice),
+// destination by destination, chunk by chunk.
 constexpr uint32_t kStreamBlock = 256;  // threads per workgroup, four columns each
 constexpr uint32_t kStreamChunk = 4 * kStreamBlock;
 // n / d without a branch: t = umulhi(n, mul), (t + ((n - t) >> s1)) >> s2;
@@ -245,12 +252,13 @@ struct StreamArgs {
   uint32_t cols;            // batch * n flat columns, < 2^32 - kStreamChunk
   uint32_t n, q, m;         // instance length, n / P, n % P
   uint32_t big;             // m * (q + 1): columns of an instance in its first m blocks (q + 1 each)
-  uint32_t flat;            // 1: every column's result is on rank 0; 0: block b's on rank b (q >= kStreamChunk)
+  uint32_t flat;            // 1: the reducing launch ran on flat columns; 0: on block tiles (q >= kStreamChunk)
   uint32_t chunks;          // ceil(cols / kStreamChunk)
   uint32_t id0;             // id of this launch's first workgroup (a multiple of C * P)
   uint32_t regions;         // 1: XCD x takes the x-th C / X chunks of a slice; 0: every X-th chunk
   uint32_t xcd_shift;       // log2 of the XCD count X (a power of two; C is a multiple of X)
   uint32_t per_xcd;         // C / X
+  uint32_t order_forced;    // 1: regions (or not) by an override, not by the size rules
   StreamDiv ndiv, q1div, qdiv;  // n, q + 1, q
   StreamDiv cdiv, sdiv;     // C (a multiple of the XCD count), C * P
   void* user[kMaxP];

@@ -2,32 +2,28 @@
 //
 // For the schedules whose distribution phase hands every rank the same
 // result (bandwidth-optimal plans of Sec. 7 in either group, and the Ring of
-// Sec. 6), the column kernels can store block b's result on rank b alone;
-// the broadcast then copies it to ranks b+1, ..., b+P-1.  The copy moves the
-// bytes the distribution phase moves, and one more read and write of each
-// block than the single fused launch.  It pays at large P: a launch that
-// reads P streams and writes P streams at once interleaves reads and writes
-// across hundreds of DRAM rows, while a reducing launch (P reads, one
-// write) and the broadcast (one read, P - 1 writes) each stream in one
-// direction.  On MI355X at P = 127 the pair with the tiled broadcast ran 8%
-// faster than the single launch (reducing 6.4 TB/s, broadcasting 5.8 TB/s,
-// single launch 5.35 TB/s), and the destination-major broadcast (second
-// kernel below, 6.3-6.4 TB/s) gains another 3-4% where it applies.
+// Sec. 6), the column kernels can store every column's result on rank 0
+// alone; the broadcast then copies rank 0's columns to ranks 1, ..., P-1.
+// The copy moves the bytes the distribution phase moves, and one more read
+// of each column and one fewer write of it than the single fused launch
+// (the reducing launch's).  It pays because a launch that reads P streams
+// and writes P streams at once interleaves reads and writes across hundreds
+// of DRAM rows, while a reducing launch (P reads, one write) and the
+// broadcast (one read, P - 1 writes) each stream in one direction.
 //
-// broadcast_kernel, the tiled copy: layout and tiles as in the reducing
-// launch (col_tile_column, device_common.hpp): one wave per 64 columns of
-// one block of one instance, tiles laid on 256-byte boundaries of rank b's
-// buffer, or one short block of several instances per wave.  After a
-// reducing launch on flat columns (a.flat: batches of short blocks) every
-// column's result is on rank 0, and the waves take 64 consecutive flat
-// columns each.  Loads and stores are nontemporal (NT) or ordinary: from
-// P = 96 ranks, streaming the P - 1 stores nontemporally at one resident
-// workgroup per CU was 3-4% faster, and on flat columns nontemporal stores
-// were 1-11% faster at any P; below P = 96 on block tiles, ordinary stores
-// streamed as fast or faster.
+// broadcast_kernel, the tiled copy: tiles as in the reducing launch
+// (col_tile_column, device_common.hpp), or 64 consecutive flat columns per
+// wave; every wave writes the P - 1 destinations of its columns.  It serves
+// the calls the kernel below does not: rank spans under the size rule of
+// capi.cpp, and index spaces beyond 32 bits.  Loads and stores are
+// nontemporal (NT) or ordinary: from P = 96 ranks, streaming the P - 1
+// stores nontemporally at one resident workgroup per CU was 3-4% faster, and
+// on flat columns nontemporal stores were 1-11% faster at any P; below
+// P = 96 on block tiles, ordinary stores streamed as fast or faster.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstring>
 
 #include "ar_internal.hpp"
 #include "device_common.hpp"
@@ -43,7 +39,6 @@ __global__ __launch_bounds__(kBlock) void broadcast_kernel(const ColArgs a) {
   const int32_t P = a.P;
   for (uint32_t t = blockIdx.x * uint32_t(kWavesPerBlock) + wave_in_block; t < a.total_tiles;
        t += gridDim.x * uint32_t(kWavesPerBlock)) {
-    int32_t b = 0;
     int64_t e;
     bool live;
     if (a.flat) {
@@ -52,13 +47,13 @@ __global__ __launch_bounds__(kBlock) void broadcast_kernel(const ColArgs a) {
       e = int64_t(inst) * a.stride + int64_t(g - inst * a.ndiv.d);
       live = g < a.flat_cols;
     } else {
+      int32_t b;
       live = col_tile_column(a, t, lane, b, e);
     }
-    void* const* rot = a.user + b;  // rot[d] is rank (b + d) mod P
     if (live) {
-      const T v = ld1<NT>(static_cast<const T*>(rot[0]) + e);
+      const T v = ld1<NT>(static_cast<const T*>(a.user[0]) + e);
 #pragma unroll 8
-      for (int32_t d = 1; d < P; ++d) st1<NT>(static_cast<T*>(rot[d]) + e, v);
+      for (int32_t d = 1; d < P; ++d) st1<NT>(static_cast<T*>(a.user[d]) + e, v);
     }
   }
 }
@@ -74,117 +69,223 @@ __global__ __launch_bounds__(kBlock) void broadcast_kernel(const ColArgs a) {
 // per slice a multiple of the XCD count X, workgroup c of a slice runs on
 // XCD c mod X for every destination.  The chunk it copies is chunk c
 // (interleaved: 1 MB of each slice per XCD, in 4 KB pieces X chunks apart),
-// or with a.regions the ((c mod X) * C / X + c / X)-th (XCD x copies the x-th
-// contiguous C / X chunks: 256 KB of each slice).  Interleaved chunks stop
-// hitting L2 at P = 110-128 below 256 MB per rank (P = 127, 64 MB per rank:
-// 36% of the source reads went to HBM), where regions keep them; regions
-// also suit blocks on the chunk grid.  With C not a multiple of X the copy
-// took 1.3x the time, with 2 MB per XCD 1.4x, and with the index arithmetic
-// behind branches (each deferring an argument load, a round trip per
-// workgroup) 1.2x.  The chunks of a slice that fall in destination y's own
-// block are skipped (y holds that result already), and a chunk holds at most
-// two blocks (the host asks for blocks of at least kStreamChunk elements),
-// or one root (flat columns).
+// or in XCD regions the ((c mod X) * C / X + c / X)-th (XCD x copies the x-th
+// contiguous C / X chunks: 256 KB of each slice).  With C not a multiple of
+// X the copy took 1.3x the time, and with 2 MB per XCD 1.4x.
+//
+// Rank buffers need no common alignment: each destination has its own chunk
+// grid, laid on the 128-byte lines of its buffer (its first chunk starts up
+// to 31 columns before column 0), so that every store but those of its two
+// ends covers whole lines, and the unaligned side is the source's, which L2
+// serves.  What bounds the copy is the stores; a store that straddled lines
+// wrote each of them twice.  Rows packed back to back at an odd length, 1 GB
+// in all, P = 8-127: 6.4-7.6 TB/s, the rate of rows on line boundaries, where
+// chunks on a common grid (the same column for every destination) moved
+// 5.2-6.8 and the tiled copy, which such calls took before, 2.6-3.3.
+//
+// All sources are rank 0's row: a chunk has one source whatever the blocks,
+// with no look-up of its root.  (With block b's result on rank b, a chunk
+// across a block boundary needed two loads and a select per element.)
+//
+// GAP: instances with a gap between them (stride > n).  The column space is
+// then the memory span of a rank's instances, and a 16-byte group that
+// touches a gap is copied element by element, which leaves the gap as it is.
+//
+// A workgroup does little besides its index arithmetic, so that arithmetic
+// has no branch before the bounds check and its words lie first and
+// together: one load of the kernel's arguments, one of the two rank
+// pointers, then the copy.  (With the chunk order behind a branch and the
+// words apart, and the second pointer loaded after the check, the copy took
+// 2-5% longer.)  LINES = false, every destination on a line boundary, is
+// kept for the same reason: its bounds check waits for no pointer.
+struct BcastArgs {
+  StreamDiv sdiv, cdiv;  // C * P, C (chunks per slice, a multiple of the XCD count X)
+  // chunk of workgroup c of a slice: (c & mask) * per_xcd + (c >> shift) --
+  // regions: X - 1, C / X, log2 X; interleaved (chunk c itself): 0, 0, 0
+  uint32_t mask, per_xcd, shift;
+  uint32_t chunks;  // chunks of the longest destination grid
+  uint32_t cols;    // columns of a rank's span: (instances - 1) * stride + n
+  uint32_t n;       // GAP: instance length
+  uint32_t P;
+  StreamDiv stdiv;  // GAP: the instance stride
+  void* user[kMaxP];
+};
+
 __device__ __forceinline__ uint32_t sdiv(uint32_t n, const StreamDiv& d) {
   const uint32_t t = __umulhi(n, d.mul);
   return (t + ((n - t) >> d.s1)) >> d.s2;
 }
 
-// Root of flat column g: rank 0 on flat columns, else the block of g within
-// its instance.  No branches, so that the argument loads are not deferred
-// into them (each deferred load is a round trip in every workgroup).
-__device__ __forceinline__ uint32_t stream_root(const StreamArgs& a, uint32_t g) {
-  const uint32_t i = g - sdiv(g, a.ndiv) * a.n;
-  const uint32_t lo = sdiv(i, a.q1div), hi = a.m + sdiv(i - a.big, a.qdiv);
-  return a.flat ? 0u : (i < a.big ? lo : hi);
-}
+// 16 bytes at any 4-byte boundary (global memory takes such accesses whole).
+typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// First column after block b0 of the instance holding column `first`
-// (block b0 + 1 = P: the instance's end), for block tiles.
-__device__ __forceinline__ uint32_t stream_block_end(const StreamArgs& a, uint32_t first, uint32_t b0) {
-  const uint32_t i0 = first - sdiv(first, a.ndiv) * a.n;
-  return first - i0 + (b0 + 1) * a.q + min(b0 + 1, a.m);
-}
-
-// STRADDLE: some block or instance boundary is off the kStreamChunk grid,
-// so chunks can span two blocks; such a chunk is copied in whole 16-byte
-// groups, each element selected from its root's load (the elements of y's
-// own block are rewritten with the value y holds: the same bits).  Without
-// STRADDLE only the tail of the column space (and any chunk across a
-// boundary, which the host rules out) takes the element path.  Both kinds
-// are kept because the instructions on the plain path matter: a workgroup
-// does little besides its index arithmetic.  At P = 127, n = 2^26
-// (straddles) the element path took 5.37 ms, whole groups 4.82 ms, and whole
-// groups behind a separate plain path 4.94 ms; at P = 128 (none) the kernel
-// with the plain path first took 4.64 ms and the whole-group one 4.80 ms.
-template <bool NT, bool STRADDLE>
-__global__ __launch_bounds__(kStreamBlock) void broadcast_stream_kernel(const StreamArgs a) {
-  const uint32_t id = a.id0 + blockIdx.x;
+// LINES: the chunk grid of a destination starts on a 128-byte line of its
+// buffer; else on column 0.
+template <bool NT, bool GAP, bool LINES>
+__global__ __launch_bounds__(kStreamBlock) void broadcast_stream_kernel(const BcastArgs a) {
+  const uint32_t id = blockIdx.x;
   const uint32_t s = sdiv(id, a.sdiv);
   const uint32_t r = id - s * a.sdiv.d;
   const uint32_t y = sdiv(r, a.cdiv);
-  uint32_t c = r - y * a.cdiv.d;  // workgroup c of the slice runs on XCD c mod X
-  if (a.regions) c = (c & ((1u << a.xcd_shift) - 1u)) * a.per_xcd + (c >> a.xcd_shift);
-  const uint32_t chunk = s * a.cdiv.d + c;
-  const uint32_t first = chunk * kStreamChunk;
-  const uint32_t last = min(first + kStreamChunk, a.cols) - 1;
-  const uint32_t b0 = stream_root(a, first), b1 = stream_root(a, last);
-  if (chunk >= a.chunks || (b0 == y && b1 == y)) return;
-  const uint32_t g = first + threadIdx.x * 4u;
-  int32_t* dst = static_cast<int32_t*>(a.user[y]);
-  const int32_t* s0 = static_cast<const int32_t*>(a.user[b0]);
-  if constexpr (STRADDLE) {
-    if (first + kStreamChunk <= a.cols) {
-      i32x4 v = *reinterpret_cast<const i32x4*>(s0 + g);
-      if (b0 != b1) {  // block b0 ends at column bnd of this chunk
-        const int32_t* s1 = static_cast<const int32_t*>(a.user[b1]);
-        const i32x4 w = *reinterpret_cast<const i32x4*>(s1 + g);
-        const uint32_t bnd = stream_block_end(a, first, b0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = g + uint32_t(i) < bnd ? v[i] : w[i];
-      }
-      if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<i32x4*>(dst + g));
-      else *reinterpret_cast<i32x4*>(dst + g) = v;
-      return;
-    }
-  } else {
-    if (b0 == b1 && first + kStreamChunk <= a.cols) {
-      const i32x4 v = *reinterpret_cast<const i32x4*>(s0 + g);
-      if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<i32x4*>(dst + g));
-      else *reinterpret_cast<i32x4*>(dst + g) = v;
-      return;
+  const uint32_t c = r - y * a.cdiv.d;  // workgroup c of the slice runs on XCD c mod X
+  const uint32_t chunk = s * a.cdiv.d + (c & a.mask) * a.per_xcd + (c >> a.shift);
+  int32_t* const row = static_cast<int32_t*>(a.user[y]);
+  const int32_t* const row0 = static_cast<const int32_t*>(a.user[0]);
+  uint32_t ph = 0;
+  if constexpr (LINES) {
+    ph = uint32_t(reinterpret_cast<uintptr_t>(row) >> 2) & 31u;
+    asm volatile("" ::"s"(row0));  // both pointers are loaded before the check that needs one of them
+  }
+  // Positions are columns plus ph, so position 0 is the start of a line;
+  // positions [ph, cols + ph) hold columns.  What is left of the span from
+  // the chunk's start on is compared, not positions past it: near 2^32
+  // columns those wrap.
+  const uint32_t u0 = chunk * kStreamChunk;
+  if ((chunk >= a.chunks) | (y == 0) | (u0 >= a.cols + ph)) return;
+  const uint32_t left = a.cols + ph - u0;
+  const uint32_t v = threadIdx.x * 4u;
+  const int64_t e0 = int64_t(u0) - int64_t(ph);  // the chunk's first column (below 0: the grid's lead)
+  int32_t* dst = row + e0 + v;
+  const int32_t* src = row0 + e0 + v;
+  bool whole = left >= kStreamChunk && u0 >= ph;
+  uint32_t i0 = 0;
+  if constexpr (GAP) {
+    whole = u0 + v >= ph && v + 4u <= left;
+    if (whole) {
+      const uint32_t m = u0 + v - ph;
+      i0 = m - sdiv(m, a.stdiv) * a.stdiv.d;
+      whole = i0 + 4u <= a.n;
     }
   }
-  // the chunk at the end of the column space (and, without STRADDLE, any
-  // chunk across a boundary): element by element
-  const int32_t* s1 = static_cast<const int32_t*>(a.user[b1]);
-  const uint32_t bnd = a.flat ? a.cols : stream_block_end(a, first, b0);
-  const bool w0 = b0 != y, w1 = b1 != y;
+  if (whole) {
+    const i32x4 w = *reinterpret_cast<const i32x4u*>(src);
+    if constexpr (NT) __builtin_nontemporal_store(i32x4u(w), reinterpret_cast<i32x4u*>(dst));
+    else *reinterpret_cast<i32x4u*>(dst) = w;
+    return;
+  }
+  // the two ends of the span, and groups that touch a gap
 #pragma unroll
   for (uint32_t i = 0; i < 4; ++i) {
-    const uint32_t gi = g + i;
-    const bool lo = gi < bnd;
-    if (gi < a.cols && (lo ? w0 : w1)) st1<NT>(dst + gi, (lo ? s0 : s1)[gi]);
+    bool live = u0 + v + i >= ph && v + i < left;
+    if constexpr (GAP) {
+      if (live) {
+        const uint32_t m = u0 + v + i - ph;
+        live = m - sdiv(m, a.stdiv) * a.stdiv.d < a.n;
+      }
+    }
+    if (live) st1<NT>(dst + i, src[i]);
   }
+}
+
+// LDS that a workgroup of the copy reserves and does not use in regions
+// order, so that four are resident on a CU, where eight fit: with fewer
+// stores in flight each XCD's sweep stays in fewer DRAM rows.  P = 127 at 72 MB
+// per rank: 7.38 against 7.16 TB/s (rows off the lines 7.19 against 6.79),
+// P = 128 at 64 MB 7.37 against 7.15; three a CU: 6.4.  Interleaved chunks
+// (one sweep for the whole chip) and copies with gaps ran within 2% either
+// way or slower with it.
+constexpr uint32_t kCopyLds = 39 * 1024;
+
+void launch_copy(const BcastArgs& a, uint32_t grid, bool nt, bool gap, bool lines, hipStream_t s) {
+  const dim3 g(grid), blk(kStreamBlock);
+  const uint32_t lds = a.mask != 0 && !gap ? kCopyLds : 0;
+#define AR_COPY(GAP, LINES)                                                                               \
+  do {                                                                                                    \
+    if (nt) hipLaunchKernelGGL((broadcast_stream_kernel<true, GAP, LINES>), g, blk, lds, s, a);             \
+    else hipLaunchKernelGGL((broadcast_stream_kernel<false, GAP, LINES>), g, blk, lds, s, a);               \
+  } while (0)
+  if (gap) AR_COPY(true, true);
+  else if (lines) AR_COPY(false, true);
+  else AR_COPY(false, false);
+#undef AR_COPY
+}
+
+// Launches the destination-major copy over a filled-in span, or returns
+// false when its grid would reach 2^32 work-items.  The slices of a call are
+// evened out and rounded up to the XCD count (a short last slice in regions
+// leaves most XCDs idle): at most 1 MB per XCD interleaved, 256 KB in regions
+// (at 8-32 MB per rank 1 MB regions ran 3-50% slower; from 64 MB the sizes ran
+// within a few percent).
+bool launch_dest_major(BcastArgs& a, uint32_t xcds, bool regions, bool gap, bool nt, hipStream_t s) {
+  uint32_t shift = 0;
+  while ((1u << shift) < xcds) ++shift;
+  const bool reg = regions && (1u << shift) == xcds;
+  bool lines = false;
+  for (uint32_t x = 1; x < a.P; ++x) lines |= reinterpret_cast<uintptr_t>(a.user[x]) % 128 != 0;
+  const uint64_t chunks = (uint64_t(a.cols) + (lines ? 31 : 0) + kStreamChunk - 1) / kStreamChunk;
+  const uint64_t cmax = (reg ? 64u : 256u) * xcds;
+  const uint64_t slices = (chunks + cmax - 1) / cmax;
+  const uint64_t C = ((chunks + slices - 1) / slices + xcds - 1) / xcds * xcds;
+  const uint64_t grid = (chunks + C - 1) / C * C * a.P;
+  if (grid > uint64_t(UINT32_MAX) / kStreamBlock) return false;
+  a.chunks = uint32_t(chunks);
+  a.cdiv = stream_div(uint32_t(C));
+  a.sdiv = stream_div(uint32_t(C) * a.P);
+  a.mask = reg ? xcds - 1 : 0;
+  a.shift = reg ? shift : 0;
+  a.per_xcd = reg ? uint32_t(C) / xcds : 0;
+  launch_copy(a, uint32_t(grid), nt, gap, lines, s);
+  return true;
 }
 
 }  // namespace
 
-int launch_broadcast_stream(const StreamArgs& a, bool nt, bool straddle, uint32_t grid, void* stream) {
+constexpr int64_t kCopyRegionsMinBytes = int64_t(16) << 20;
+
+int launch_broadcast_stream(const StreamArgs& a, bool nt, bool /*straddle*/, uint32_t grid, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const dim3 g(grid), blk(kStreamBlock);
-  if (straddle) {
-    if (nt) hipLaunchKernelGGL((broadcast_stream_kernel<true, true>), g, blk, 0, s, a);
-    else hipLaunchKernelGGL((broadcast_stream_kernel<false, true>), g, blk, 0, s, a);
-  } else {
-    if (nt) hipLaunchKernelGGL((broadcast_stream_kernel<true, false>), g, blk, 0, s, a);
-    else hipLaunchKernelGGL((broadcast_stream_kernel<false, false>), g, blk, 0, s, a);
+  BcastArgs b;
+  std::memset(&b, 0, sizeof b);
+  b.P = a.P;
+  b.cols = a.cols;
+  b.n = a.n;
+  b.stdiv = StreamDiv{1, 0, 0, 0};
+  std::memcpy(b.user, a.user, sizeof b.user);
+  // every source on rank 0's row, the order no longer depends on the blocks:
+  // unless it is forced, regions above kCopyRegionsMinBytes per rank, whose
+  // slices then fill the chip (P = 127 at 256 MB: 4.67-4.70 ms against
+  // 4.89-4.96 interleaved; at 18 MB 0.347-0.351 against 0.350-0.355, at 4.5 MB
+  // 0.092 against 0.084)
+  const bool regions = a.order_forced ? a.regions != 0 : int64_t(a.cols) * 4 > kCopyRegionsMinBytes;
+  if (!launch_dest_major(b, 1u << a.xcd_shift, regions, false, nt, s)) {
+    // a grid just below 2^32 work-items that the line-aligned grids' extra
+    // chunk takes past it: the common grid
+    b.chunks = a.chunks;
+    b.cdiv = a.cdiv;
+    b.sdiv = a.sdiv;
+    b.mask = a.regions ? (1u << a.xcd_shift) - 1 : 0;
+    b.shift = a.regions ? a.xcd_shift : 0;
+    b.per_xcd = a.regions ? a.per_xcd : 0;
+    launch_copy(b, grid, nt, false, false, s);
   }
   return int(hipGetLastError());
 }
 
+// Rank buffers off 16-byte boundaries, or gaps between the instances: the
+// destination-major copy too wherever the size rule of capi.cpp asks for it
+// (a.dest_major) and a rank's span fits its 32-bit positions.  With gaps,
+// instances that start off 32-byte sectors (a stride that is no multiple of
+// 8) or hold fewer than 512 elements take cached stores, which leave the
+// parts of a line that different workgroups write to meet in L2, in
+// interleaved order: P = 37, 65536 x 106, stride 113: 3.1 TB/s against 2.0
+// nontemporal; P = 64, 8192 x 2304, stride 2311: 5.75 against 5.55; strides
+// 2328 and 1024 the other way round, 5.5 against 6.2 and 5.25 against 6.0.
 int launch_broadcast(const ColArgs& a, int dtype, bool nt, int grid, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  const int64_t span = (a.instances - 1) * a.stride + a.n;
+  if (a.dest_major && span <= int64_t(UINT32_MAX) - 2 * kStreamChunk) {
+    const bool gap = a.instances > 1 && a.stride != a.n;
+    BcastArgs b;
+    std::memset(&b, 0, sizeof b);
+    b.P = uint32_t(a.P);
+    b.cols = uint32_t(span);
+    b.n = uint32_t(a.n);
+    b.stdiv = stream_div(gap ? uint32_t(a.stride) : 1u);
+    std::memcpy(b.user, a.user, sizeof b.user);
+    const bool sectors = !gap || (a.stride % 8 == 0 && a.n >= 512);
+    if (launch_dest_major(b, a.xcds, a.bcast_regions != 0 && sectors, gap, a.bcast_nt != 0 && sectors, s))
+      return int(hipGetLastError());
+  }
   const dim3 g(grid), blk(kBlock);
   if (dtype == 0) {
     if (nt) hipLaunchKernelGGL((broadcast_kernel<int32_t, true>), g, blk, a.lds, s, a);

@@ -69,7 +69,9 @@ constexpr int32_t kBcastStreamMinP = 96;
 // 5-10% less time than regions) or from kBcastInterleaveMinBytes per rank
 // (P = 127 at 256 MB: 5%), and regions otherwise, where the interleaved
 // chunks read their sources from L2 no more (P = 127 below 256 MB per rank:
-// 1.1-2.0x the time of regions).
+// 1.1-2.0x the time of regions).  (The block-tile figures are those of a
+// copy whose sources lay on every block's own rank; with every source on
+// rank 0, launch_broadcast_stream applies the flat rule to them too.)
 constexpr int64_t kBcastStreamMinBytes = int64_t(2) << 20;
 constexpr int64_t kBcastFlatInterleaveMaxBytes = int64_t(16) << 20;
 constexpr int64_t kBcastInterleaveMinBytes = int64_t(256) << 20;
@@ -592,6 +594,8 @@ ar_status run_fused_col(ar_plan* pl, void* const* bufs, int64_t batch, int64_t s
   a.r = s.r;
   a.split = pl->fused_split ? 1 : 0;
   a.stride = stride;
+  a.n = s.n;
+  a.instances = batch;
   a.q = s.n / s.P;
   a.m = s.n % s.P;
   const int64_t max_len = a.q + (a.m ? 1 : 0);
@@ -661,17 +665,22 @@ ar_status run_fused_col(ar_plan* pl, void* const* bufs, int64_t batch, int64_t s
     else if (a.flat) regions = span > kBcastFlatInterleaveMaxBytes;
     else if (!straddle) regions = s.P >= kBcastRegionMinP || span >= kBcastAlignedRegionMinBytes;
     else regions = s.P >= kBcastRegionMinP && span < kBcastInterleaveMinBytes;
+    // the destination-major copy: nontemporal at any P (launches of
+    // kFusedNtThresholdBytes and more).  Alone, its cached stores were up
+    // to 6% faster on some shapes (P = 64 at 16 MB per rank, flat columns),
+    // but the pair then took 0.3-10% longer: the next reducing launch pays
+    // for the cached lines (P = 32-128, 4-256 MB per rank, flat and block)
+    const bool snt = pl->bcast_nt_mode == 1 || (pl->bcast_nt_mode < 0 && big);
     if (want_stream && stream_bcast_args(pl, bufs, batch, stride, a.flat != 0, regions, device, &sa)) {
+      sa.order_forced = pl->bcast_stream_mode >= 2 ? 1 : 0;
       const uint32_t sgrid = (sa.chunks + sa.cdiv.d - 1) / sa.cdiv.d * sa.sdiv.d;
-      // the destination-major copy: nontemporal at any P (launches of
-      // kFusedNtThresholdBytes and more).  Alone, its cached stores were up
-      // to 6% faster on some shapes (P = 64 at 16 MB per rank, flat columns),
-      // but the pair then took 0.3-10% longer: the next reducing launch pays
-      // for the cached lines (P = 32-128, 4-256 MB per rank, flat and block)
-      const bool snt = pl->bcast_nt_mode == 1 || (pl->bcast_nt_mode < 0 && big);
       e = ar::launch_broadcast_stream(sa, snt, straddle, sgrid, stream);
     } else {
       a.lds = cap_lds(pl->bcast_cap, device);
+      a.xcds = stream_slice_chunks(device) / 256;
+      a.dest_major = want_stream ? 1 : 0;
+      a.bcast_regions = regions ? 1 : 0;
+      a.bcast_nt = snt ? 1 : 0;
       e = ar::launch_broadcast(a, pl->dtype, bnt, grid, stream);
     }
     if (e != 0) return hip_fail(hipError_t(e), "broadcast kernel launch");

@@ -15,10 +15,10 @@
 // is read once and every output written once (2 * P * n elements of HBM
 // traffic instead of 5 * (P - 1) * n).
 //
-// With a.split set, only the root rank b receives the result and a second
-// launch (broadcast.hip) copies it to the other ranks: the same bits, one
-// more read and write of a block per column, but the reading and the writing
-// of the P streams no longer interleave (see the broadcast kernel).
+// With a.split set, only rank 0 receives the result and a second launch
+// (broadcast.hip) copies it to the other ranks: the same bits, one more read
+// of each column, but the reading and the writing of the P streams no longer
+// interleave (see the broadcast kernel).
 //
 // One wave covers 64 consecutive columns of one block of one instance, one
 // 4-byte element per lane: the block, hence the rotation of the rank
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void fused_bo_kernel(const ColArgs a) {
       for (int d = 0; d < P; ++d) w[d] = ld1<NT>(static_cast<const T*>(rot[d]) + e);
       bo_fold<P, OP, T, P>(w);
       if (a.split) {
-        st1<NT>(static_cast<T*>(rot[0]) + e, w[0]);
+        st1<NT>(static_cast<T*>(a.user[0]) + e, w[0]);
       } else {
 #pragma unroll
         for (int d = 0; d < P; ++d) st1<NT>(static_cast<T*>(rot[d]) + e, w[0]);

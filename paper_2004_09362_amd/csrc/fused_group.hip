@@ -33,7 +33,7 @@
 // buffer, or one short block of several instances per wave -- the tiling of
 // the cyclic column kernels (col_tile_column, device_common.hpp).  Where
 // every rank receives the same result (the Ring, Recursive Halving) a split
-// launch stores it to the root rank b only and broadcast.hip copies it on.
+// launch stores it to rank 0 only and broadcast.hip copies it on.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -123,8 +123,8 @@ __global__ __launch_bounds__(kBlock) void fused_xor_kernel(const ColArgs a) {
       for (int y = 0; y < P; ++y) X[y] = ld1<NT>(static_cast<const T*>(tbl[y]) + e);
       xor_halving<P, W, P / 2, OP, T>(X, uint32_t(b));
       xor_doubling<P, W, W / 2, OP, T>(X);
-      if (W == 1 && a.split) {  // Recursive Halving: one result, held first by rank b (rank 0 on flat columns)
-        st1<NT>(static_cast<T*>(tbl[a.flat ? 0 : b]) + e, X[0]);
+      if (W == 1 && a.split) {  // Recursive Halving: one result, held first by rank 0
+        st1<NT>(static_cast<T*>(tbl[0]) + e, X[0]);
       } else {
 #pragma unroll
         for (int x = 0; x < P; ++x) st1<NT>(static_cast<T*>(tbl[x]) + e, X[x & (W - 1)]);
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kBlock) void fused_ring_kernel(const ColArgs a) {
       for (int d = 1; d <= D; ++d)
         if (d < P) acc = comb<OP>(v[d - 1], acc);
       if (a.split) {
-        st1<NT>(static_cast<T*>(rot[0]) + e, acc);
+        st1<NT>(static_cast<T*>(a.user[0]) + e, acc);
       } else {
 #pragma unroll
         for (int d = 0; d <= D; ++d)
