@@ -562,6 +562,8 @@ def kernel_name(args, dj, st, fused):
     """Name of the dominant job's kernel(s) as the profiles list it."""
     if not fused:
         kname = "step_kernel<k=%d>" % dj["k"]
+    elif str(dj.get("dtype", "float32")) == "int32":
+        kname = "fused_free_kernel<P=%d>" % dj["P"]
     elif st.fused_flat and args.group != "xor":
         kname = "fused_rot_kernel<P=%d,%s>" % (dj["P"], "ring" if args.schedule == "ring" else "r=%d" % st.r)
     elif args.schedule == "ring":

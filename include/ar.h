@@ -179,14 +179,18 @@ typedef struct {
                                         launch and a broadcast (every rank receives the
                                         same result and P >= 64; P >= 24 when n * e is
                                         at least 32 MiB; P >= 33 in the rank-slot
-                                        kernel)                                          */
+                                        kernel).  int32 plans, whose combinations give
+                                        the same bits in any order, have one result at
+                                        every k and split for P >= 17 when n * e is at
+                                        least 4 MiB or P * n * e at least 192 MiB        */
   int32_t fused_flat;                /* FUSED path with short blocks (sums; max in the
                                         bandwidth-optimal, Ring and XOR plans), and on
                                         long blocks the AR_FUSED_ROTATE defaults: 1
                                         when it runs on
                                         flat columns (the rank-slot kernel, or the XOR
                                         group's kernel without the block) for batches of
-                                        fewer than 2^32 - 64 columns                     */
+                                        fewer than 2^32 - 64 columns (the fp32 kernels'
+                                        choice: the int32 kernel has no block tiles)     */
   int32_t exec_path;                 /* path ar_execute takes: AR_PATH_STEPWISE or
                                         AR_PATH_FUSED (AR_PATH_AUTO resolved); 0 when
                                         there is nothing to run (P = 1)                  */

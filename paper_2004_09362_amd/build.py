@@ -17,14 +17,17 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libar.so")
 SOURCES = [os.path.join(CSRC, f) for f in ["plan.cpp", "capi.cpp", "kernels.hip", "fused_lo.hip", "fused_group.hip",
+                                           "fused_free.hip",
                                            "broadcast.hip", "noalloc.hip"]]
-HEADERS = [os.path.join(CSRC, f) for f in ("ar_internal.hpp", "device_common.hpp", "fused_col.hpp")] + [
+HEADERS = [os.path.join(CSRC, f) for f in ("ar_internal.hpp", "device_common.hpp", "fused_col.hpp",
+                                               "fused_free.hpp")] + [
     os.path.join(ROOT, "include", "ar.h")]
 OBJDIR = os.path.join(HERE, "_build")
 GENDIR = os.path.join(OBJDIR, "gen")
 
 # The column-fused kernels (fused_col.hpp) are instantiated once per P =
-# 2..128 -- bandwidth-optimal, shifted and rank-slot launchers -- in COL_UNITS
+# 2..128 -- bandwidth-optimal, shifted and rank-slot launchers, and the int32
+# kernel of fused_free.hpp -- in COL_UNITS
 # generated units that share the P values round-robin, so that they compile
 # in parallel.  Fifteen of them (about 90 s each) and fused_group.hip (about
 # 60 s), started first, keep eight cores busy to the end: about 180 s in all,
@@ -38,10 +41,11 @@ def col_unit_text(i: int) -> str:
     2 + i + COL_UNITS, ..."""
     lines = ["// Generated by paper_2004_09362_amd/build.py: instantiations of the column-fused",
              "// kernels of fused_col.hpp for every %d-th P starting at %d." % (COL_UNITS, 2 + i),
-             '#include "fused_col.hpp"', "", "namespace ar {", ""]
+             '#include "fused_col.hpp"', '#include "fused_free.hpp"', "", "namespace ar {", ""]
     for P in range(2 + i, 129, COL_UNITS):
         for kind in COL_KINDS:
             lines.append("template int launch_fused_%s<%d>(const ColArgs&, int, int, bool, int, void*);" % (kind, P))
+        lines.append("template int launch_free_at<%d>(const FreeArgs&, int, int, bool, int, uint32_t, void*);" % P)
     lines += ["", "}  // namespace ar", ""]
     return "\n".join(lines)
 
@@ -127,6 +131,7 @@ FAMILIES = {
     "lo": ["fused_lo.hip"],
     "col": ["fused_col.hpp"],  # and the generated units (col_unit_text)
     "group": ["fused_group.hip"],
+    "free": ["fused_free.hip", "fused_free.hpp"],
     "bcast": ["broadcast.hip"],
 }
 
@@ -138,7 +143,7 @@ def kernel_families(kernel: str) -> list[str]:
     for part in kernel.split("+"):
         for prefix, fam in (("step_kernel", "step"), ("fused_lo_kernel", "lo"), ("fused_bo_kernel", "col"),
                             ("fused_mid_kernel", "col"), ("fused_rot_kernel", "col"), ("fused_xor_kernel", "group"),
-                            ("fused_ring_kernel", "group"), ("broadcast", "bcast")):
+                            ("fused_ring_kernel", "group"), ("fused_free_kernel", "free"), ("broadcast", "bcast")):
             if part.startswith(prefix):
                 out.append(fam)
                 break

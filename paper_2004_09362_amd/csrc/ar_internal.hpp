@@ -144,6 +144,19 @@ struct StepArgs {
   uint32_t run_cols[kMaxRanges], tile_first[kMaxRanges];
 };
 
+// What the host decided about a fused launch beyond its work, for launchers
+// that choose their own shape: nontemporal accesses (0 / 1 by override, -1
+// open), whether that is to be nontemporal when open (launches of
+// kFusedNtThresholdBytes and more), the bytes the call moves, and an
+// overriding occupancy cap.
+struct FusedTuning {
+  int64_t bytes;
+  int32_t nt;
+  int32_t big;
+  int32_t cap_forced;
+  uint32_t lds;  // the overriding cap's LDS
+};
+
 // lds: dynamic LDS each workgroup reserves without using it, so that fewer
 // workgroups are resident per CU (0: no cap); read by the launchers.
 struct FusedArgs {
@@ -151,6 +164,7 @@ struct FusedArgs {
   int64_t n, stride, batch;
   int64_t groups;           // column groups (16-byte mode) or columns (other modes)
   uint32_t lds;
+  FusedTuning tune;
 };
 
 // Column kernels: wave tile t -> (instance, block, 64 columns of the block).
@@ -189,6 +203,7 @@ struct ColArgs {
   int64_t n, instances;
   uint32_t xcds;
   int32_t dest_major, bcast_regions, bcast_nt;
+  FusedTuning tune;
 };
 
 // dtype: 0 int32, 1 float32; op: 0 sum, 1 max.  Returns a hipError_t value.
@@ -196,6 +211,25 @@ int launch_step(const StepArgs& a, int dtype, int op, bool vec, bool nt, int gri
 // One step as merged runs (a.run_len, a.tiles, ...): each range's blocks of a
 // rank streamed as one flat space per instance.
 int launch_step_merged(const StepArgs& a, int dtype, int op, bool nt, int grid, void* stream);
+// Any int32 plan (fused_free.hip): every rank, or rank 0 with `split`,
+// receives the combination of the P values of each column.  The launchers
+// below hand their int32 calls to it.
+int launch_fused_free(void* const* user, int P, int op, int64_t n, int64_t stride, int64_t instances, bool split,
+                      const FusedTuning& tune, void* stream);
+// Its kernel's arguments and launcher, one instantiation per P (units written
+// by build.py).
+struct FreeArgs {
+  void* user[kMaxP];
+  int32_t split;
+  int32_t gaps;        // 0: no gaps between instances; 1: gaps; 2: gaps and 2^32 groups or more
+  int64_t n, stride;   // instance length (without gaps the whole span's) and stride
+  int64_t groups;      // lanes with work: instances * gpi
+  int64_t gpi;         // groups of V elements per instance (the last one may hold fewer)
+  uint64_t blocks;     // workgroups with work (the grid's loop)
+  FastDiv gdiv;        // gpi
+};
+template <int P>
+int launch_free_at(const FreeArgs& a, int V, int op, bool nt, int grid, uint32_t lds, void* stream);
 // Fused latency-optimal kernel; mode 1: one element per lane (contiguous
 // instances), 2: any instance stride.
 int launch_fused_lo(const FusedArgs& a, int P, int dtype, int op, int mode, bool nt, int grid, void* stream);

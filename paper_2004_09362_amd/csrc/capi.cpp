@@ -39,6 +39,14 @@ constexpr int64_t kFusedNtThresholdBytes = int64_t(128) << 20;
 constexpr int32_t kSplitMinP = 64;
 constexpr int32_t kSplitMidMinP = 24;
 constexpr int64_t kSplitMidMinBytes = int64_t(32) << 20;
+// int32 plans (any k, group and schedule: one result) split from
+// kFreeSplitMinP ranks where an instance holds kFreeSplitMinBytes per rank or
+// kFreeSplitMinTotal over all ranks.  On one launch / split, TB/s: P = 24 at
+// 4 MB per rank 5.0 / 4.7, at 16 MB 5.6 / 6.1, at 128 MB 6.1 / 6.45; P = 64 at
+// 2 MB 5.5 / 5.3, at 16 MB 5.8 / 6.9; P = 127 at 1 MB 5.5 / 4.6, at 2 MB 5.25 /
+// 5.85; P = 16 at 128 MB 6.4 / 6.1, off the 128-byte lines 5.6 / 6.0.
+constexpr int32_t kFreeSplitMinP = 17;
+constexpr int64_t kFreeSplitMinBytes = int64_t(4) << 20, kFreeSplitMinTotal = int64_t(192) << 20;
 // Flat short-block sums in the rank-slot kernel (not the XOR group's) split
 // from this many ranks up: their single launch streams 5.0-5.6 TB/s there and
 // the pair up to 6.0 (P = 37: 7%, P = 48: 15% faster with caps 4 and 2 and a
@@ -197,6 +205,7 @@ struct ar_plan {
   // Occupancy caps (resident workgroups per CU; 0: none) of the fused launch
   // and of the broadcast that follows a split one (AR_FUSED_CAP overrides).
   int32_t fused_cap = 0, bcast_cap = 0;
+  bool cap_forced = false;
   int32_t path = AR_PATH_AUTO;
   int32_t fused_kind = kFusedNone;
   bool fused_ok = false;
@@ -430,6 +439,12 @@ bool use_nt(int32_t mode, int64_t bytes, int64_t threshold = kNtThresholdBytes) 
   return mode == 1 || (mode < 0 && bytes >= threshold);
 }
 
+// The tuning of a fused call that moves `bytes` (ar_internal.hpp).
+ar::FusedTuning tuning(const ar_plan* pl, int64_t bytes, int device) {
+  return ar::FusedTuning{bytes, pl->fused_nt_mode, bytes >= kFusedNtThresholdBytes ? 1 : 0,
+                         pl->cap_forced ? 1 : 0, pl->cap_forced ? cap_lds(pl->fused_cap, device) : 0};
+}
+
 // Timing-only HIP events (no system-scope fence) recorded on the launch
 // stream before the first launch of an execute and after each launch
 // (ar_execute_timed).  The first failure is kept; the events are destroyed
@@ -571,6 +586,7 @@ ar_status run_fused_lo(ar_plan* pl, void* const* bufs, int64_t batch, int64_t st
   const bool contiguous = (batch == 1 || stride == s.n);
   const int mode = contiguous ? 1 : 2;
   a.groups = cols;
+  a.tune = tuning(pl, int64_t(2) * s.P * cols * 4, device);
   int64_t blocks = (a.groups + 255) / 256;
   blocks = std::min<int64_t>(std::max<int64_t>(blocks, 1), int64_t(1) << 22);
   const bool nt = mode == 1 && use_nt(pl->fused_nt_mode, int64_t(2) * s.P * cols * 4, kFusedNtThresholdBytes);
@@ -639,6 +655,7 @@ ar_status run_fused_col(ar_plan* pl, void* const* bufs, int64_t batch, int64_t s
   const bool nt = use_nt(pl->fused_nt_mode, int64_t(2) * s.P * s.n * batch * 4, kFusedNtThresholdBytes);
   const int grid = ar::step_grid(a.total_tiles);
   a.lds = cap_lds(pl->fused_cap, device);
+  a.tune = tuning(pl, int64_t(2) * s.P * s.n * batch * 4, device);
   if (tm) tm->mark();
   int e;
   if (pl->fused_kind == kFusedXor) e = ar::launch_fused_xor(a, s.P, pl->dtype, pl->op, nt, grid, stream);
@@ -712,7 +729,7 @@ ar_status execute_impl(ar_plan* plan, void* const* rank_buffers, int64_t batch, 
     return fail(AR_ERR_NO_DEVICE, std::string("no usable GPU: ") + hipGetErrorString(he));
   }
   const bool fused = plan->path == AR_PATH_FUSED || (plan->path == AR_PATH_AUTO && plan->fused_ok);
-  if (fused && plan->fused_kind != kFusedLo) {
+  if (fused && (plan->fused_kind != kFusedLo || plan->fused_split)) {
     st = run_fused_col(plan, rank_buffers, batch, instance_stride, stream, device, tm);
   } else if (fused) {
     st = run_fused_lo(plan, rank_buffers, batch, instance_stride, stream, device, tm);
@@ -851,8 +868,11 @@ ar_status create_plan(int32_t P, int64_t n, ar_dtype dtype, ar_op op, int32_t k_
   else if (pl->s.P <= ar::kFusedMaxP && pl->s.r == pl->s.L) pl->fused_kind = kFusedLo;
   else pl->fused_kind = kFusedCol;
   pl->fused_ok = pl->fused_kind != kFusedNone;
-  // one result for every rank: the Ring, and r = 0 outside the flat LO kernel
-  const bool one_result = pl->fused_kind == kFusedRing ||
+  // one result for every rank: the Ring, r = 0 outside the flat LO kernel, and
+  // every int32 plan, whose combinations give the same bits in any order
+  const bool any_order = pl->s.P >= 2 && pl->dtype == AR_INT32;
+  const bool one_result = any_order ||
+pl->fused_kind == kFusedRing ||
                           ((pl->fused_kind == kFusedCol || pl->fused_kind == kFusedXor) && pl->s.r == 0);
   {
     const int64_t max_len = pl->s.P > 0 ? pl->s.n / pl->s.P + (pl->s.n % pl->s.P ? 1 : 0) : 0;
@@ -882,7 +902,10 @@ ar_status create_plan(int32_t P, int64_t n, ar_dtype dtype, ar_op op, int32_t k_
   const bool rank_slots = pl->fused_flat && pl->fused_kind != kFusedXor;
   const int32_t split_min =
       rank_slots ? kFlatSplitMinP : (pl->s.n * 4 >= kSplitMidMinBytes ? kSplitMidMinP : kSplitMinP);
-  pl->fused_split = one_result && (pl->split_mode == 1 || (pl->split_mode < 0 && pl->s.P >= split_min));
+  const bool split_by_size = any_order ? pl->s.P >= kFreeSplitMinP && (pl->s.n * 4 >= kFreeSplitMinBytes ||
+                                                                       pl->s.n * 4 >= kFreeSplitMinTotal / pl->s.P)
+                                       : pl->s.P >= split_min;
+  pl->fused_split = one_result && (pl->split_mode == 1 || (pl->split_mode < 0 && split_by_size));
   {
     const int32_t P = pl->s.P;
     if (pl->fused_split) pl->fused_cap = (rank_slots && P < kSplitMinP) ? 4 : 6;
@@ -899,6 +922,7 @@ ar_status create_plan(int32_t P, int64_t n, ar_dtype dtype, ar_op op, int32_t k_
     const char* ce = std::getenv("AR_FUSED_CAP");
     if (ce != nullptr && ce[0] >= '0' && ce[0] <= '9') {
       pl->fused_cap = pl->bcast_cap = cap_of(ce);
+      pl->cap_forced = true;
       const char* comma = std::strchr(ce, ',');
       if (comma != nullptr && comma[1] >= '0' && comma[1] <= '9') pl->bcast_cap = cap_of(comma + 1);
     }

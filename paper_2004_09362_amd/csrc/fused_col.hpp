@@ -345,50 +345,39 @@ int launch_rot_rr(const ColArgs& a, int grid, hipStream_t s) {
 // instantiations.
 template <int P>
 int launch_fused_rot(const ColArgs& a, int dtype, int op, bool ring, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const dim3 g(grid), blk(kBlock);
   if (op == 1) {
     if (ring) {
-      if (dtype == 0) hipLaunchKernelGGL((fused_rot_kernel<P, -1, int32_t, 1>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 1>), g, blk, a.lds, s, a);
+      hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 1>), g, blk, a.lds, s, a);
     } else if constexpr (P >= kRotMaxShiftedMinP && P <= kRotMaxShiftedMaxP) {
-      return dtype == 0 ? launch_rot_rr<P, 0, int32_t, 1>(a, grid, s) : launch_rot_rr<P, 0, float, 1>(a, grid, s);
+      return launch_rot_rr<P, 0, float, 1>(a, grid, s);
     } else {
       if (a.r != 0) return int(hipErrorInvalidValue);
-      if (dtype == 0) hipLaunchKernelGGL((fused_rot_kernel<P, 0, int32_t, 1>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_rot_kernel<P, 0, float, 1>), g, blk, a.lds, s, a);
+      hipLaunchKernelGGL((fused_rot_kernel<P, 0, float, 1>), g, blk, a.lds, s, a);
     }
     return int(hipGetLastError());
   }
   if (op != 0) return int(hipErrorInvalidValue);
   if (ring) {
-    if (dtype == 0) hipLaunchKernelGGL((fused_rot_kernel<P, -1, int32_t, 0>), g, blk, a.lds, s, a);
-    else hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 0>), g, blk, a.lds, s, a);
+    hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 0>), g, blk, a.lds, s, a);
     return int(hipGetLastError());
   }
-  return dtype == 0 ? launch_rot_rr<P, 0, int32_t, 0>(a, grid, s) : launch_rot_rr<P, 0, float, 0>(a, grid, s);
+  return launch_rot_rr<P, 0, float, 0>(a, grid, s);
 }
 
 template <int P>
 int launch_fused_bo(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const dim3 g(grid), blk(kBlock);
-  if (dtype == 0) {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, int32_t, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_bo_kernel<P, int32_t, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, int32_t, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_bo_kernel<P, int32_t, 1, false>), g, blk, a.lds, s, a);
-    }
+  if (op == 0) {
+    if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, float, 0, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_bo_kernel<P, float, 0, false>), g, blk, a.lds, s, a);
   } else {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, float, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_bo_kernel<P, float, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, float, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_bo_kernel<P, float, 1, false>), g, blk, a.lds, s, a);
-    }
+    if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, float, 1, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_bo_kernel<P, float, 1, false>), g, blk, a.lds, s, a);
   }
   return int(hipGetLastError());
 }
@@ -399,24 +388,15 @@ namespace ar {
 
 template <int P>
 int launch_fused_mid(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const dim3 g(grid), blk(kBlock);
-  if (dtype == 0) {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, int32_t, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_mid_kernel<P, int32_t, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, int32_t, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_mid_kernel<P, int32_t, 1, false>), g, blk, a.lds, s, a);
-    }
+  if (op == 0) {
+    if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, float, 0, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_mid_kernel<P, float, 0, false>), g, blk, a.lds, s, a);
   } else {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, float, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_mid_kernel<P, float, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, float, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_mid_kernel<P, float, 1, false>), g, blk, a.lds, s, a);
-    }
+    if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, float, 1, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_mid_kernel<P, float, 1, false>), g, blk, a.lds, s, a);
   }
   return int(hipGetLastError());
 }

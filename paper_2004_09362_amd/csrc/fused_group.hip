@@ -171,56 +171,36 @@ __global__ __launch_bounds__(kBlock) void fused_ring_kernel(const ColArgs a) {
 }
 
 template <int NC>
-int launch_ring_nc(const ColArgs& a, int dtype, int op, bool nt, int grid, hipStream_t s) {
+int launch_ring_nc(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
   const dim3 g(grid), blk(kBlock);
-  if (dtype == 0) {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, int32_t, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_ring_kernel<NC, int32_t, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, int32_t, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_ring_kernel<NC, int32_t, 1, false>), g, blk, a.lds, s, a);
-    }
+  if (op == 0) {
+    if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, float, 0, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_ring_kernel<NC, float, 0, false>), g, blk, a.lds, s, a);
   } else {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, float, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_ring_kernel<NC, float, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, float, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_ring_kernel<NC, float, 1, false>), g, blk, a.lds, s, a);
-    }
+    if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, float, 1, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_ring_kernel<NC, float, 1, false>), g, blk, a.lds, s, a);
   }
   return int(hipGetLastError());
 }
 
 template <int P, int R>
-int launch_xor_pr(const ColArgs& a, int dtype, int op, bool nt, int grid, hipStream_t s) {
+int launch_xor_pr(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
   const dim3 g(grid), blk(kBlock);
-  if (dtype == 0) {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, int32_t, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_xor_kernel<P, R, int32_t, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, int32_t, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_xor_kernel<P, R, int32_t, 1, false>), g, blk, a.lds, s, a);
-    }
+  if (op == 0) {
+    if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 0, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 0, false>), g, blk, a.lds, s, a);
   } else {
-    if (op == 0) {
-      if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 0, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 0, false>), g, blk, a.lds, s, a);
-    } else {
-      if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 1, true>), g, blk, a.lds, s, a);
-      else hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 1, false>), g, blk, a.lds, s, a);
-    }
+    if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 1, true>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 1, false>), g, blk, a.lds, s, a);
   }
   return int(hipGetLastError());
 }
 
 template <int P, int R>
-int launch_xor_r(const ColArgs& a, int dtype, int op, bool nt, int grid, hipStream_t s) {
+int launch_xor_r(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
   if constexpr ((1 << R) <= P) {
-    if (a.r == R) return launch_xor_pr<P, R>(a, dtype, op, nt, grid, s);
-    return launch_xor_r<P, R + 1>(a, dtype, op, nt, grid, s);
+    if (a.r == R) return launch_xor_pr<P, R>(a, op, nt, grid, s);
+    return launch_xor_r<P, R + 1>(a, op, nt, grid, s);
   } else {
     return int(hipErrorInvalidValue);
   }
@@ -229,30 +209,32 @@ int launch_xor_r(const ColArgs& a, int dtype, int op, bool nt, int grid, hipStre
 }  // namespace
 
 int launch_fused_xor(const ColArgs& a, int P, int dtype, int op, bool nt, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   switch (P) {
-    case 2: return launch_xor_r<2, 0>(a, dtype, op, nt, grid, s);
-    case 4: return launch_xor_r<4, 0>(a, dtype, op, nt, grid, s);
-    case 8: return launch_xor_r<8, 0>(a, dtype, op, nt, grid, s);
-    case 16: return launch_xor_r<16, 0>(a, dtype, op, nt, grid, s);
-    case 32: return launch_xor_r<32, 0>(a, dtype, op, nt, grid, s);
-    case 64: return launch_xor_r<64, 0>(a, dtype, op, nt, grid, s);
-    case 128: return launch_xor_r<128, 0>(a, dtype, op, nt, grid, s);
+    case 2: return launch_xor_r<2, 0>(a, op, nt, grid, s);
+    case 4: return launch_xor_r<4, 0>(a, op, nt, grid, s);
+    case 8: return launch_xor_r<8, 0>(a, op, nt, grid, s);
+    case 16: return launch_xor_r<16, 0>(a, op, nt, grid, s);
+    case 32: return launch_xor_r<32, 0>(a, op, nt, grid, s);
+    case 64: return launch_xor_r<64, 0>(a, op, nt, grid, s);
+    case 128: return launch_xor_r<128, 0>(a, op, nt, grid, s);
     default: return int(hipErrorInvalidValue);
   }
 }
 
 int launch_fused_ring(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, a.P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   switch ((a.P - 2) / kRingChunk) {  // P - 1 ranks after the root, in chunks of 16
-    case 0: return launch_ring_nc<1>(a, dtype, op, nt, grid, s);
-    case 1: return launch_ring_nc<2>(a, dtype, op, nt, grid, s);
-    case 2: return launch_ring_nc<3>(a, dtype, op, nt, grid, s);
-    case 3: return launch_ring_nc<4>(a, dtype, op, nt, grid, s);
-    case 4: return launch_ring_nc<5>(a, dtype, op, nt, grid, s);
-    case 5: return launch_ring_nc<6>(a, dtype, op, nt, grid, s);
-    case 6: return launch_ring_nc<7>(a, dtype, op, nt, grid, s);
-    case 7: return launch_ring_nc<8>(a, dtype, op, nt, grid, s);
+    case 0: return launch_ring_nc<1>(a, op, nt, grid, s);
+    case 1: return launch_ring_nc<2>(a, op, nt, grid, s);
+    case 2: return launch_ring_nc<3>(a, op, nt, grid, s);
+    case 3: return launch_ring_nc<4>(a, op, nt, grid, s);
+    case 4: return launch_ring_nc<5>(a, op, nt, grid, s);
+    case 5: return launch_ring_nc<6>(a, op, nt, grid, s);
+    case 6: return launch_ring_nc<7>(a, op, nt, grid, s);
+    case 7: return launch_ring_nc<8>(a, op, nt, grid, s);
     default: return int(hipErrorInvalidValue);
   }
 }

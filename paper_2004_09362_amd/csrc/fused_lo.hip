@@ -10,7 +10,7 @@
 // (2*P*n elements).  The latency-optimal tree of rank x is the same for
 // every block, so many small instances form one flat column space with no
 // block index: the kernel for many independent small messages (Sec. 1's
-// 425-byte average).
+// 425-byte average).  fp32 only (int32 plans: fused_free.hip).
 //
 // Compiled with packed-fp32 instructions disabled; only adds and compares.
 #include <hip/hip_runtime.h>
@@ -35,17 +35,6 @@ constexpr int lo_N(int P, int i) {
   return N;
 }
 
-template <typename V, int OP>
-struct Comb;
-template <int OP>
-struct Comb<float, OP> {
-  __device__ __forceinline__ static float f(float a, float b) { return comb<OP>(a, b); }
-};
-template <int OP>
-struct Comb<int32_t, OP> {
-  __device__ __forceinline__ static int32_t f(int32_t a, int32_t b) { return comb<OP>(a, b); }
-};
-
 // Reduction step I of the latency-optimal schedule on one column: with
 // f = floor(N_I/2), every rank receives the primed vector of rank x + f;
 // starred sums take it on even N_I, primed sums on every step but the last.
@@ -63,8 +52,8 @@ __device__ __forceinline__ void lo_steps(V (&R)[P], V (&S)[P]) {
 #pragma unroll
     for (int x = 0; x < P; ++x) {
       const V recv = R[(x + f) % P];
-      if constexpr (even) S[x] = Comb<V, OP>::f(S[x], recv);
-      if constexpr (!last) Rn[x] = Comb<V, OP>::f(R[x], recv);
+      if constexpr (even) S[x] = comb<OP>(S[x], recv);
+      if constexpr (!last) Rn[x] = comb<OP>(R[x], recv);
     }
     if constexpr (!last) {
 #pragma unroll
@@ -128,9 +117,8 @@ int launch_fused_t(const FusedArgs& a, int P, int mode, bool nt, int grid, hipSt
 }  // namespace
 
 int launch_fused_lo(const FusedArgs& a, int P, int dtype, int op, int mode, bool nt, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.batch, false, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (dtype == 0)
-    return op == 0 ? launch_fused_t<int32_t, 0>(a, P, mode, nt, grid, s) : launch_fused_t<int32_t, 1>(a, P, mode, nt, grid, s);
   return op == 0 ? launch_fused_t<float, 0>(a, P, mode, nt, grid, s) : launch_fused_t<float, 1>(a, P, mode, nt, grid, s);
 }
 
