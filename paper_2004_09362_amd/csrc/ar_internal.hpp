@@ -155,7 +155,29 @@ struct FusedTuning {
   int32_t big;
   int32_t cap_forced;
   uint32_t lds;  // the overriding cap's LDS
+  int32_t layout_forced;  // 1: the column layout is an override's (AR_FUSED_PACKED, AR_FUSED_ROTATE)
 };
+
+// Whether every rank buffer starts on a 128-byte line, and whether they all
+// start at the same place within one.
+inline bool rows_on_lines(void* const* user, int P) {
+  for (int x = 0; x < P; ++x)
+    if (reinterpret_cast<uintptr_t>(user[x]) % 128 != 0) return false;
+  return true;
+}
+inline bool rows_congruent(void* const* user, int P) {
+  for (int x = 1; x < P; ++x)
+    if ((reinterpret_cast<uintptr_t>(user[x]) ^ reinterpret_cast<uintptr_t>(user[0])) % 128 != 0) return false;
+  return true;
+}
+
+// LDS that lets `cap` workgroups fit on a CU (160 KB), 0 for no cap.
+constexpr uint32_t cap_lds_bytes(int cap) {
+  return cap == 0 ? 0u : cap == 1 ? 84u * 1024 : (160u * 1024 / uint32_t(cap) - 1024) / 512 * 512;
+}
+// Calls that move less than this run from the caches to a good part: tight
+// occupancy caps then leave too few waves to hide latency behind.
+constexpr int64_t kTightCapBytes = int64_t(256) << 20;
 
 // lds: dynamic LDS each workgroup reserves without using it, so that fewer
 // workgroups are resident per CU (0: no cap); read by the launchers.
@@ -165,6 +187,7 @@ struct FusedArgs {
   int64_t groups;           // column groups (16-byte mode) or columns (other modes)
   uint32_t lds;
   FusedTuning tune;
+  FastDiv ndiv;             // n, for gaps between instances (set by the launcher)
 };
 
 // Column kernels: wave tile t -> (instance, block, 64 columns of the block).

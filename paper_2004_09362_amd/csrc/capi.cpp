@@ -442,7 +442,8 @@ bool use_nt(int32_t mode, int64_t bytes, int64_t threshold = kNtThresholdBytes) 
 // The tuning of a fused call that moves `bytes` (ar_internal.hpp).
 ar::FusedTuning tuning(const ar_plan* pl, int64_t bytes, int device) {
   return ar::FusedTuning{bytes, pl->fused_nt_mode, bytes >= kFusedNtThresholdBytes ? 1 : 0,
-                         pl->cap_forced ? 1 : 0, pl->cap_forced ? cap_lds(pl->fused_cap, device) : 0};
+                         pl->cap_forced ? 1 : 0, pl->cap_forced ? cap_lds(pl->fused_cap, device) : 0,
+                         pl->packed_mode >= 0 || pl->rotate_mode >= 0 ? 1 : 0};
 }
 
 // Timing-only HIP events (no system-scope fence) recorded on the launch

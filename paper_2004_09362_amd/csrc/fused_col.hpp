@@ -271,9 +271,8 @@ __device__ __forceinline__ void rot_gather(T (&Z)[P], const T (&S)[P], std::inte
 // parameter so that the compiler drops the starred sums that no rank
 // receives (all but 2^RR of them) and the primed sums that only feed those
 // (at P = 127, RR = 4: 306 of 1524 combinations); with all of them kept,
-// the P = 127 kernels spilled registers.  Loads and stores are always
-// nontemporal: these launches stream short blocks of many instances once.
-template <int P, int RR, typename T, int OP>
+// the P = 127 kernels spilled registers.
+template <int P, int RR, typename T, int OP, bool NT>
 __global__ __launch_bounds__(kBlock) void fused_rot_kernel(const ColArgs a) {
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -292,7 +291,7 @@ __global__ __launch_bounds__(kBlock) void fused_rot_kernel(const ColArgs a) {
       const int64_t e = int64_t(inst) * a.stride + i;
       T X[P];
 #pragma unroll
-      for (int y = 0; y < P; ++y) X[y] = ld1<true>(static_cast<const T*>(tbl[y]) + e);
+      for (int y = 0; y < P; ++y) X[y] = ld1<NT>(static_cast<const T*>(tbl[y]) + e);
       rotate_lanes<P, 0, T>(X, b);
       if constexpr (RR <= 0) {
         T acc;
@@ -305,10 +304,10 @@ __global__ __launch_bounds__(kBlock) void fused_rot_kernel(const ColArgs a) {
           acc = X[0];
         }
         if (a.split) {  // every rank receives acc: rank 0 holds it first, the broadcast copies it
-          st1<true>(static_cast<T*>(tbl[0]) + e, acc);
+          st1<NT>(static_cast<T*>(tbl[0]) + e, acc);
         } else {
 #pragma unroll
-          for (int y = 0; y < P; ++y) st1<true>(static_cast<T*>(tbl[y]) + e, acc);
+          for (int y = 0; y < P; ++y) st1<NT>(static_cast<T*>(tbl[y]) + e, acc);
         }
       } else {
         T S[P];
@@ -319,20 +318,20 @@ __global__ __launch_bounds__(kBlock) void fused_rot_kernel(const ColArgs a) {
         rot_gather<P, RR, T>(X, S, std::make_integer_sequence<int, P>{});
         rotate_lanes<P, 0, T>(X, b == 0 ? 0u : uint32_t(P) - b);
 #pragma unroll
-        for (int y = 0; y < P; ++y) st1<true>(static_cast<T*>(tbl[y]) + e, X[y]);
+        for (int y = 0; y < P; ++y) st1<NT>(static_cast<T*>(tbl[y]) + e, X[y]);
       }
     }
   }
 }
 
-template <int P, int RR, typename T, int OP>
+template <int P, int RR, int OP, bool NT>
 int launch_rot_rr(const ColArgs& a, int grid, hipStream_t s) {
   if constexpr (RR < col_L(P)) {
     if (a.r == RR) {
-      hipLaunchKernelGGL((fused_rot_kernel<P, RR, T, OP>), dim3(grid), dim3(kBlock), a.lds, s, a);
+      hipLaunchKernelGGL((fused_rot_kernel<P, RR, float, OP, NT>), dim3(grid), dim3(kBlock), a.lds, s, a);
       return int(hipGetLastError());
     }
-    return launch_rot_rr<P, RR + 1, T, OP>(a, grid, s);
+    return launch_rot_rr<P, RR + 1, OP, NT>(a, grid, s);
   } else {
     return int(hipErrorInvalidValue);
   }
@@ -341,36 +340,164 @@ int launch_rot_rr(const ColArgs& a, int grid, hipStream_t s) {
 // Sums at every r; max (op 1) for the bandwidth-optimal fold and the Ring,
 // whose ranks all receive one result, and at every r for P in
 // [kRotMaxShiftedMinP, kRotMaxShiftedMaxP].  Elsewhere shifted max plans
-// keep the block or packed tiles, which saves most of the max
-// instantiations.
-template <int P>
-int launch_fused_rot(const ColArgs& a, int dtype, int op, bool ring, int grid, void* stream) {
-  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+// reach this kernel from launch_fused_mid, on short blocks, in its cached
+// form alone.  int32 plans have their own kernel.  Nontemporal on the lines
+// whatever the size: these launches stream short blocks of many instances once.
+template <int P, bool NT>
+int launch_rot_nt(const ColArgs& a, int op, bool ring, int grid, hipStream_t s) {
   const dim3 g(grid), blk(kBlock);
   if (op == 1) {
     if (ring) {
-      hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 1>), g, blk, a.lds, s, a);
+      hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 1, NT>), g, blk, a.lds, s, a);
     } else if constexpr (P >= kRotMaxShiftedMinP && P <= kRotMaxShiftedMaxP) {
-      return launch_rot_rr<P, 0, float, 1>(a, grid, s);
+      return launch_rot_rr<P, 0, 1, NT>(a, grid, s);
     } else {
       if (a.r != 0) return int(hipErrorInvalidValue);
-      hipLaunchKernelGGL((fused_rot_kernel<P, 0, float, 1>), g, blk, a.lds, s, a);
+      hipLaunchKernelGGL((fused_rot_kernel<P, 0, float, 1, NT>), g, blk, a.lds, s, a);
     }
     return int(hipGetLastError());
   }
   if (op != 0) return int(hipErrorInvalidValue);
   if (ring) {
-    hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 0>), g, blk, a.lds, s, a);
+    hipLaunchKernelGGL((fused_rot_kernel<P, -1, float, 0, NT>), g, blk, a.lds, s, a);
     return int(hipGetLastError());
   }
-  return launch_rot_rr<P, 0, float, 0>(a, grid, s);
+  return launch_rot_rr<P, 0, 0, NT>(a, grid, s);
+}
+
+template <int P>
+int launch_fused_rot(const ColArgs& a, int dtype, int op, bool ring, int grid, void* stream) {
+  if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  return (a.split && P < 48) || flat_on_lines(a) ? launch_rot_nt<P, true>(a, op, ring, grid, s)
+                                                 : launch_rot_nt<P, false>(a, op, ring, grid, s);
+}
+
+// fused_wide_kernel: the block-tiled plans of few ranks (P <= 8, r < L) with
+// four columns per lane.  With P rows of 256 bytes in flight per wave, few
+// ranks leave the memory system short of requests, and the tile arithmetic of
+// a wave weighs on its few loads; a lane's 16-byte rows also split fewer lines
+// where the rank buffers share no alignment.  One launch of 2^26 elements per
+// rank, TB/s, 4-byte lanes / this kernel: P = 2 4.7 / 6.4, P = 3 5.5 / 6.4, P = 4
+// 5.9 / 6.3; rows off the lines, 1 GB in all: P = 4 4.85 / 5.9, P = 5 4.8 / 5.6,
+// P = 8 4.1 / 5.75.  On the lines from P = 5 up 4-byte lanes stream as fast.
+// Blocks of kWideMinLen elements and more: a lane that straddles the end of
+// its block does its columns one by one.
+constexpr int kWideMaxP = 8, kWideCols = 4;
+constexpr int64_t kWideMinLen = 1024;
+
+template <int RR, int V, bool NT, int P, int... Qs>
+__device__ __forceinline__ void wide_store(void* const* rot, int64_t e, const float (&S)[P][V],
+                                           std::integer_sequence<int, Qs...>) {
+  (stv<V, NT>(static_cast<float*>(rot[Qs]) + e, S[std::integral_constant<int, col_src(P, RR, Qs)>::value]), ...);
+}
+
+template <int P, int RR, int V, int OP, bool NT>
+__device__ __forceinline__ void wide_cols(const ColArgs& a, void* const* rot, int64_t e) {
+  float x[P][V], S[P][V];
+#pragma unroll
+  for (int d = 0; d < P; ++d) ldv<V, NT>(x[d], static_cast<const float*>(rot[d]) + e);
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    float R[P], Si[P];
+#pragma unroll
+    for (int d = 0; d < P; ++d) R[d] = Si[d] = x[d][i];
+    if constexpr (RR == 0) {
+      bo_fold<P, OP, float, P>(R);
+      S[0][i] = R[0];
+    } else {
+      mid_steps<P, 0, OP, float>(R, Si);
+#pragma unroll
+      for (int d = 0; d < P; ++d) S[d][i] = Si[d];
+    }
+  }
+  if constexpr (RR != 0) {
+    wide_store<RR, V, NT, P>(rot, e, S, std::make_integer_sequence<int, P>{});
+  } else if (a.split) {
+    stv<V, NT>(static_cast<float*>(a.user[0]) + e, S[0]);
+  } else {
+#pragma unroll
+    for (int d = 0; d < P; ++d) stv<V, NT>(static_cast<float*>(rot[d]) + e, S[0]);
+  }
+}
+
+template <int P, int RR, int OP, bool NT>
+__global__ __launch_bounds__(kBlock) void fused_wide_kernel(const ColArgs a) {
+  constexpr int V = kWideCols;
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  for (uint32_t t = blockIdx.x * uint32_t(kWavesPerBlock) + wave_in_block; t < a.total_tiles;
+       t += gridDim.x * uint32_t(kWavesPerBlock)) {
+    const uint32_t seg = fdiv(t, a.tiles);  // seg = instance * P + block
+    const uint32_t tile = t - seg * a.tiles.d;
+    const uint32_t inst = fdiv(seg, a.pdiv);
+    const int32_t b = int32_t(seg - inst * a.pdiv.d);
+    const int64_t len = a.q + (b < a.m ? 1 : 0);
+    const int64_t e0 = int64_t(inst) * a.stride + int64_t(b) * a.q + (b < a.m ? b : a.m);
+    const int64_t lo = ((reinterpret_cast<uintptr_t>(a.user[b]) >> 2) + e0) & (kWave * V - 1);
+    const int64_t c = int64_t(tile) * (kWave * V) - lo + lane * V;
+    void* const* rot = a.user + b;  // rot[d] is rank (b + d) mod P
+    if (c >= 0 && c + V <= len) {
+      wide_cols<P, RR, V, OP, NT>(a, rot, e0 + c);
+    } else {
+      for (int i = 0; i < V; ++i)
+        if (c + i >= 0 && c + i < len) wide_cols<P, RR, 1, OP, NT>(a, rot, e0 + c + i);
+    }
+  }
+}
+
+template <int P, int RR>
+int launch_wide_rr(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
+  if constexpr (RR < col_L(P)) {
+    if (a.r != RR) return launch_wide_rr<P, RR + 1>(a, op, nt, grid, s);
+    const dim3 g(grid), blk(kBlock);
+    if constexpr (P <= 4) {
+      if (nt) {
+        if (op == 0) hipLaunchKernelGGL((fused_wide_kernel<P, RR, 0, true>), g, blk, a.lds, s, a);
+        else hipLaunchKernelGGL((fused_wide_kernel<P, RR, 1, true>), g, blk, a.lds, s, a);
+        return int(hipGetLastError());
+      }
+    }
+    if (op == 0) hipLaunchKernelGGL((fused_wide_kernel<P, RR, 0, false>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_wide_kernel<P, RR, 1, false>), g, blk, a.lds, s, a);
+    return int(hipGetLastError());
+  } else {
+    return int(hipErrorInvalidValue);
+  }
+}
+
+// Whether a launch takes the wide lanes: any rows up to four ranks, rows off
+// the lines up to eight (cached: with nontemporal accesses forced, not), and
+// not between kFusedNtThresholdBytes and kTightCapBytes, where 4-byte lanes
+// with more waves ran 5% faster.
+template <int P>
+bool wide_lanes(const ColArgs& a) {
+  return P <= kWideMaxP && !a.flat && !a.packed && a.r < col_L(P) && a.q >= kWideMinLen &&
+         (!a.tune.big || a.tune.bytes >= kTightCapBytes) &&
+         (P <= 4 || (a.tune.nt != 1 && !rows_congruent(a.user, P))) &&
+         a.instances * P * ((a.q + 1 + 2 * kWave * kWideCols) / (kWave * kWideCols)) < (int64_t(1) << 31);
+}
+
+template <int P>
+int launch_wide(const ColArgs& args, int op, bool nt, hipStream_t s) {
+  ColArgs a = args;
+  const int64_t len = a.q + (a.m ? 1 : 0), cols = kWave * kWideCols;
+  const int64_t tiles = (len + 2 * (cols - 1)) / cols;  // the tile grid of a block is shifted by up to cols - 1
+  a.tiles = make_fastdiv(uint32_t(tiles));
+  a.total_tiles = uint32_t(a.instances * P * tiles);
+  const bool tight = a.tune.bytes >= kTightCapBytes;
+  if (!a.tune.cap_forced) a.lds = cap_lds_bytes(!tight ? 0 : P == 2 ? 4 : P <= 4 ? 2 : 1);
+  const int64_t blocks = (int64_t(a.total_tiles) + kWavesPerBlock - 1) / kWavesPerBlock;
+  return launch_wide_rr<P, 0>(a, op, nt, int(blocks < kMaxGrid ? blocks : kMaxGrid), s);
 }
 
 template <int P>
 int launch_fused_bo(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if constexpr (P <= kWideMaxP)
+    if (wide_lanes<P>(a)) return launch_wide<P>(a, op, nt, s);
+  nt = stream_nt(a, nt);
   const dim3 g(grid), blk(kBlock);
   if (op == 0) {
     if (nt) hipLaunchKernelGGL((fused_bo_kernel<P, float, 0, true>), g, blk, a.lds, s, a);
@@ -390,6 +517,28 @@ template <int P>
 int launch_fused_mid(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if constexpr (P <= kWideMaxP)
+    if (wide_lanes<P>(a)) return launch_wide<P>(a, op, nt, s);
+  // Shifted max on short blocks: rank slots on flat columns, as shifted sums.
+  // Packed tiles touch a separate short segment per instance and rank: 65536 x
+  // 106, packed / this, P = 5 97 / 51 us, P = 8 257 / 79 us, P = 16 960 / 159 us, P = 64
+  // 17.2 / 0.70 ms; 39880 x 106, P = 127, 37.8 / 0.98 ms.
+  if constexpr (col_L(P) > 1) {
+    const int64_t cols = a.n * a.instances;
+    if (op == 1 && a.packed && !a.tune.layout_forced && a.r < col_L(P) && cols < (int64_t(1) << 32) - 64) {
+      ColArgs f = a;
+      f.packed = 0;
+      f.flat = 1;
+      f.flat_cols = uint32_t(cols);
+      f.ndiv = make_fastdiv(uint32_t(a.n));
+      f.q1div = make_fastdiv(uint32_t(a.q + 1));
+      f.qdiv = make_fastdiv(uint32_t(a.q > 0 ? a.q : 1));
+      f.total_tiles = uint32_t((cols + 63) / 64);
+      const int64_t blocks = (int64_t(f.total_tiles) + kWavesPerBlock - 1) / kWavesPerBlock;
+      return launch_rot_rr<P, 1, 1, false>(f, int(blocks < kMaxGrid ? blocks : kMaxGrid), s);
+    }
+  }
+  nt = stream_nt(a, nt);
   const dim3 g(grid), blk(kBlock);
   if (op == 0) {
     if (nt) hipLaunchKernelGGL((fused_mid_kernel<P, float, 0, true>), g, blk, a.lds, s, a);

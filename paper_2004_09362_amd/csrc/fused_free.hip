@@ -20,9 +20,6 @@ struct FreeShape {
   uint32_t lds;
 };
 
-// LDS that lets `cap` workgroups fit on a CU (160 KB), 0 for no cap.
-constexpr uint32_t free_cap_lds(int cap) { return cap == 0 ? 0u : cap == 1 ? 84u * 1024 : (160u * 1024 / cap - 1024) / 512 * 512; }
-
 // Measured on calls of 1 GB, TB/s of 2 * P * n * 4 bytes, one launch; in
 // brackets the same with 4-byte lanes, nontemporal, at the best cap:
 //   rows on 128-byte lines: 16-byte lanes at two workgroups a CU, P = 3 6.6
@@ -47,8 +44,6 @@ constexpr uint32_t free_cap_lds(int cap) { return cap == 0 ? 0u : cap == 1 ? 84u
 // hide latency behind (P = 8 at 16 MB per rank: 52 us at six workgroups a CU,
 // 56 at two; P = 13 at 16 MB: 77 us with 4-byte lanes at four, 85 with 8-byte
 // lanes at two).
-constexpr int64_t kTightCapBytes = int64_t(256) << 20;
-
 FreeShape free_shape(int P, bool split, bool lines, const FusedTuning& tune, int64_t n, bool gaps) {
   FreeShape s{};
   const bool tight = tune.bytes >= kTightCapBytes, huge = tune.bytes >= 2 * kTightCapBytes;
@@ -76,7 +71,7 @@ FreeShape free_shape(int P, bool split, bool lines, const FusedTuning& tune, int
     s.nt = lines ? P <= 65 : s.V == 4 && P <= 4;
   }
   s.nt = s.nt && tune.big != 0;
-  s.lds = free_cap_lds(cap);
+  s.lds = cap_lds_bytes(cap);
   return s;
 }
 
@@ -102,13 +97,9 @@ int launch_fused_free(void* const* user, int P, int op, int64_t n, int64_t strid
                       const FusedTuning& tune, void* stream) {
   FreeArgs a;
   std::memset(&a, 0, sizeof a);
-  bool lines = true;
-  for (int x = 0; x < P; ++x) {
-    a.user[x] = user[x];
-    lines = lines && reinterpret_cast<uintptr_t>(user[x]) % 128 == 0;
-  }
+  for (int x = 0; x < P; ++x) a.user[x] = user[x];
   const bool gaps = instances > 1 && stride != n;
-  if (gaps && stride % 32 != 0) lines = false;
+  const bool lines = rows_on_lines(user, P) && (!gaps || stride % 32 == 0);
   a.split = split ? 1 : 0;
   a.n = gaps ? n : instances * n;
   a.stride = stride;

@@ -24,50 +24,6 @@
 
 namespace ar {
 
-template <int V>
-struct IntVec;
-template <>
-struct IntVec<1> {
-  typedef int32_t U;
-};
-// at any 4-byte boundary: global memory takes such accesses whole
-template <>
-struct IntVec<2> {
-  typedef int32_t U __attribute__((ext_vector_type(2), aligned(4)));
-};
-template <>
-struct IntVec<4> {
-  typedef int32_t U __attribute__((ext_vector_type(4), aligned(4)));
-};
-
-template <int V, bool NT>
-__device__ __forceinline__ void free_load(int32_t (&x)[V], const int32_t* p) {
-  using U = typename IntVec<V>::U;
-  U u;
-  if constexpr (NT) u = __builtin_nontemporal_load(reinterpret_cast<const U*>(p));
-  else u = *reinterpret_cast<const U*>(p);
-  if constexpr (V == 1) {
-    x[0] = u;
-  } else {
-#pragma unroll
-    for (int i = 0; i < V; ++i) x[i] = u[i];
-  }
-}
-
-template <int V, bool NT>
-__device__ __forceinline__ void free_store(int32_t* p, const int32_t (&x)[V]) {
-  using U = typename IntVec<V>::U;
-  U u;
-  if constexpr (V == 1) {
-    u = x[0];
-  } else {
-#pragma unroll
-    for (int i = 0; i < V; ++i) u[i] = x[i];
-  }
-  if constexpr (NT) __builtin_nontemporal_store(u, reinterpret_cast<U*>(p));
-  else *reinterpret_cast<U*>(p) = u;
-}
-
 // All P rows of a lane's columns are loaded before the first combination.
 // How a lane finds its columns: without gaps (one instance, or several back
 // to back) lane g takes the elements from g * V on; with gaps, group g mod
@@ -92,17 +48,17 @@ __global__ __launch_bounds__(kBlock) void fused_free_kernel(const FreeArgs a) {
       if (V == 1 || left >= V) {
         int32_t x[P][V];
 #pragma unroll
-        for (int y = 0; y < P; ++y) free_load<V, NT>(x[y], static_cast<const int32_t*>(tbl[y]) + e);
+        for (int y = 0; y < P; ++y) ldv<V, NT>(x[y], static_cast<const int32_t*>(tbl[y]) + e);
 #pragma unroll
         for (int y = 1; y < P; ++y) {
 #pragma unroll
           for (int i = 0; i < V; ++i) x[0][i] = comb<OP>(x[0][i], x[y][i]);
         }
         if (a.split) {
-          free_store<V, NT>(static_cast<int32_t*>(tbl[0]) + e, x[0]);
+          stv<V, NT>(static_cast<int32_t*>(tbl[0]) + e, x[0]);
         } else {
 #pragma unroll
-          for (int y = 0; y < P; ++y) free_store<V, NT>(static_cast<int32_t*>(tbl[y]) + e, x[0]);
+          for (int y = 0; y < P; ++y) stv<V, NT>(static_cast<int32_t*>(tbl[y]) + e, x[0]);
         }
       } else {  // the last elements of an instance, fewer than V
         for (int64_t i = 0; i < left; ++i) {

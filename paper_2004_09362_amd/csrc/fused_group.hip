@@ -133,6 +133,65 @@ __global__ __launch_bounds__(kBlock) void fused_xor_kernel(const ColArgs a) {
   }
 }
 
+// fused_xor_wide_kernel: sums of few ranks (P <= 8) on flat columns without
+// gaps, four columns per lane, whose order does not see the block.  As in the
+// block-tiled plans of few ranks (fused_wide_kernel), four ranks and fewer
+// leave the memory system short of requests with 4-byte lanes, and up to
+// eight ranks 16-byte rows split fewer lines where the rank buffers share no
+// alignment.  One launch, TB/s, 4-byte lanes / this kernel: P = 2, 2^26 elements,
+// 4.8 / 6.5 (P = 4 6.1 / 6.1); rows off the lines, 1 GB in all, P = 4 5.2 / 5.6,
+// P = 8 4.2 / 5.8.
+constexpr int kXorWideCols = 4;
+
+template <int P, int R, int V, bool NT>
+__device__ __forceinline__ void xor_wide_cols(const ColArgs& a, int64_t e) {
+  constexpr int W = 1 << R;
+  float x[P][V];
+#pragma unroll
+  for (int y = 0; y < P; ++y) ldv<V, NT>(x[y], static_cast<const float*>(a.user[y]) + e);
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    float X[P];
+#pragma unroll
+    for (int y = 0; y < P; ++y) X[y] = x[y][i];
+    xor_halving<P, W, P / 2, 0, float>(X, 0u);
+    xor_doubling<P, W, W / 2, 0, float>(X);
+#pragma unroll
+    for (int y = 0; y < W; ++y) x[y][i] = X[y];
+  }
+  if (W == 1 && a.split) {
+    stv<V, NT>(static_cast<float*>(a.user[0]) + e, x[0]);
+  } else {
+#pragma unroll
+    for (int y = 0; y < P; ++y) stv<V, NT>(static_cast<float*>(a.user[y]) + e, x[y & (W - 1)]);
+  }
+}
+
+template <int P, int R, bool NT>
+__global__ __launch_bounds__(kBlock) void fused_xor_wide_kernel(const ColArgs a) {
+  constexpr int V = kXorWideCols;
+  for (uint32_t t = blockIdx.x; t < a.total_tiles; t += gridDim.x) {
+    const uint64_t c = (uint64_t(t) * kBlock + threadIdx.x) * V;
+    if (c + V <= a.flat_cols) {
+      xor_wide_cols<P, R, V, NT>(a, int64_t(c));
+    } else {
+      for (int i = 0; i < V; ++i)
+        if (c + i < a.flat_cols) xor_wide_cols<P, R, 1, NT>(a, int64_t(c + i));
+    }
+  }
+}
+
+template <int P, int R>
+int launch_xor_wide(const ColArgs& args, bool nt, hipStream_t s) {
+  ColArgs a = args;
+  a.total_tiles = uint32_t((uint64_t(a.flat_cols) + kBlock * kXorWideCols - 1) / (kBlock * kXorWideCols));  // workgroups
+  if (!a.tune.cap_forced) a.lds = cap_lds_bytes(a.tune.bytes < kTightCapBytes ? 0 : P == 2 ? 4 : P <= 4 ? 2 : 1);
+  const dim3 g(a.total_tiles < uint64_t(kMaxGrid) ? a.total_tiles : uint32_t(kMaxGrid)), blk(kBlock);
+  if (nt) hipLaunchKernelGGL((fused_xor_wide_kernel<P, R, true>), g, blk, a.lds, s, a);
+  else hipLaunchKernelGGL((fused_xor_wide_kernel<P, R, false>), g, blk, a.lds, s, a);
+  return int(hipGetLastError());
+}
+
 constexpr int kRingChunk = 16;
 
 // NC chunks of 16 ranks: the kernel serves 16 (NC - 1) + 1 < P <= 16 NC + 1,
@@ -172,6 +231,7 @@ __global__ __launch_bounds__(kBlock) void fused_ring_kernel(const ColArgs a) {
 
 template <int NC>
 int launch_ring_nc(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
+  nt = stream_nt(a, nt);
   const dim3 g(grid), blk(kBlock);
   if (op == 0) {
     if (nt) hipLaunchKernelGGL((fused_ring_kernel<NC, float, 0, true>), g, blk, a.lds, s, a);
@@ -185,6 +245,16 @@ int launch_ring_nc(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
 
 template <int P, int R>
 int launch_xor_pr(const ColArgs& a, int op, bool nt, int grid, hipStream_t s) {
+  // wide lanes: any rows at two ranks, rows off the lines at four (both
+  // nontemporal) and eight (cached); between kFusedNtThresholdBytes and
+  // kTightCapBytes 4-byte lanes with more waves ran 5% faster
+  if constexpr (P <= 8) {
+    const bool no_gaps = a.instances == 1 || a.stride == a.n;
+    if (op == 0 && a.flat && no_gaps && (!a.tune.big || a.tune.bytes >= kTightCapBytes) &&
+        (P == 2 || (!flat_on_lines(a) && (P <= 4 || a.tune.nt != 1))))
+      return launch_xor_wide<P, R>(a, P <= 4 && nt, s);
+  }
+  nt = stream_nt(a, nt);
   const dim3 g(grid), blk(kBlock);
   if (op == 0) {
     if (nt) hipLaunchKernelGGL((fused_xor_kernel<P, R, float, 0, true>), g, blk, a.lds, s, a);

@@ -63,38 +63,80 @@ __device__ __forceinline__ void lo_steps(V (&R)[P], V (&S)[P]) {
   }
 }
 
-// MODE 1: contiguous instances, column g = element g (4-byte accesses; 16-byte
-//         column groups measured 5-9% slower and are not built);
-// MODE 2: any instance stride, column g = element g % n of instance g / n.
-template <int P, typename T, int OP, int MODE, bool NT>
+// One lane's V columns from element e on.
+template <int P, int OP, int V, bool NT>
+__device__ __forceinline__ void lo_cols(const FusedArgs& a, int64_t e) {
+  float x[P][V];
+#pragma unroll
+  for (int y = 0; y < P; ++y) ldv<V, NT>(x[y], static_cast<const float*>(a.user[y]) + e);
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    float R[P], S[P];
+#pragma unroll
+    for (int y = 0; y < P; ++y) R[y] = S[y] = x[y][i];
+    lo_steps<P, 0, OP, float>(R, S);
+#pragma unroll
+    for (int y = 0; y < P; ++y) x[y][i] = S[y];
+  }
+#pragma unroll
+  for (int y = 0; y < P; ++y) stv<V, NT>(static_cast<float*>(a.user[y]) + e, x[y]);
+}
+
+// GAPS false: instances back to back, lane g takes the V columns from g * V on
+// (a.groups columns in all).  GAPS true: any instance stride, column g is
+// element g % n of instance g / n, V = 1; the division in 32 bits (a.ndiv)
+// where the columns fit.
+template <int P, int OP, int V, bool NT, bool GAPS>
 __global__ __launch_bounds__(kBlock) void fused_lo_kernel(const FusedArgs a) {
-  const int64_t nthreads = int64_t(gridDim.x) * kBlock;
-  for (int64_t g = int64_t(blockIdx.x) * kBlock + threadIdx.x; g < a.groups; g += nthreads) {
-    int64_t e = g;
-    if constexpr (MODE == 2) {
-      const int64_t inst = g / a.n;
-      e = inst * a.stride + (g - inst * a.n);
+  const int64_t step = int64_t(gridDim.x) * kBlock * V;
+  for (int64_t g = (int64_t(blockIdx.x) * kBlock + threadIdx.x) * V; g < a.groups; g += step) {
+    if constexpr (GAPS) {
+      const int64_t inst = a.groups <= int64_t(UINT32_MAX) ? int64_t(fdiv(uint32_t(g), a.ndiv)) : g / a.n;
+      lo_cols<P, OP, 1, NT>(a, inst * a.stride + (g - inst * a.n));
+    } else if (V == 1 || g + V <= a.groups) {
+      lo_cols<P, OP, V, NT>(a, g);
+    } else {
+      for (int64_t i = g; i < a.groups; ++i) lo_cols<P, OP, 1, NT>(a, i);
     }
-    T R[P], S[P];
-#pragma unroll
-    for (int x = 0; x < P; ++x) {
-      R[x] = ld1<NT>(reinterpret_cast<const T*>(a.user[x]) + e);
-      S[x] = R[x];
-    }
-    lo_steps<P, 0, OP, T>(R, S);
-#pragma unroll
-    for (int x = 0; x < P; ++x) st1<NT>(reinterpret_cast<T*>(a.user[x]) + e, S[x]);
   }
 }
 
+// Columns per lane: four up to three ranks (4-byte lanes leave the memory
+// system short of requests: 2^26 elements, P = 2 5.9 / 6.5 TB/s, P = 3 6.7 / 6.7) and
+// up to eight where the rows are off the 128-byte lines (P = 3 5.4 / 6.05, P = 5
+// 5.15 / 5.8, P = 8 4.6 / 5.8); else one, with which P = 4-12 on the lines streamed
+// 4-9% faster.  Accesses off the lines are cached from five ranks up
+// (stream_nt's reason).
 template <int P, typename T, int OP>
-int launch_fused_p(const FusedArgs& a, int mode, bool nt, int grid, hipStream_t s) {
-  const dim3 g(grid), blk(kBlock);
+int launch_fused_p(const FusedArgs& args, int mode, bool nt, int grid, hipStream_t s) {
+  FusedArgs a = args;
+  const dim3 blk(kBlock);
+  const bool lines = rows_on_lines(a.user, P);
   if (mode == 1) {
-    if (nt) hipLaunchKernelGGL((fused_lo_kernel<P, T, OP, 1, true>), g, blk, a.lds, s, a);
-    else hipLaunchKernelGGL((fused_lo_kernel<P, T, OP, 1, false>), g, blk, a.lds, s, a);
+    const bool wide = P <= 8 && (!a.tune.big || a.tune.bytes >= kTightCapBytes) &&
+                      (P <= 3 || (!lines && (P <= 4 || a.tune.nt != 1)));
+    if constexpr (P <= 8) {
+      if (wide) {
+        constexpr int V = 4;
+        const int64_t blocks = (a.groups + kBlock * V - 1) / (kBlock * V);
+        const dim3 g(uint32_t(blocks < kMaxGrid ? blocks : kMaxGrid));
+        if (!a.tune.cap_forced) a.lds = cap_lds_bytes(a.tune.bytes < kTightCapBytes ? 0 : P == 2 ? 4 : P <= 4 ? 2 : 1);
+        if constexpr (P <= 4) {
+          if (nt) {
+            hipLaunchKernelGGL((fused_lo_kernel<P, OP, V, true, false>), g, blk, a.lds, s, a);
+            return int(hipGetLastError());
+          }
+        }
+        hipLaunchKernelGGL((fused_lo_kernel<P, OP, V, false, false>), g, blk, a.lds, s, a);
+        return int(hipGetLastError());
+      }
+    }
+    const dim3 g(grid);
+    if (nt && (lines || a.tune.nt == 1)) hipLaunchKernelGGL((fused_lo_kernel<P, OP, 1, true, false>), g, blk, a.lds, s, a);
+    else hipLaunchKernelGGL((fused_lo_kernel<P, OP, 1, false, false>), g, blk, a.lds, s, a);
   } else if (mode == 2) {
-    hipLaunchKernelGGL((fused_lo_kernel<P, T, OP, 2, false>), g, blk, a.lds, s, a);
+    if (a.groups <= int64_t(UINT32_MAX)) a.ndiv = make_fastdiv(uint32_t(a.n));
+    hipLaunchKernelGGL((fused_lo_kernel<P, OP, 1, false, true>), dim3(grid), blk, a.lds, s, a);
   } else {
     return int(hipErrorInvalidValue);
   }
