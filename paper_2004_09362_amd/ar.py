@@ -6,18 +6,23 @@ PyTorch is used for device memory and streams: rank buffers are torch
 tensors (or raw device addresses), the stream is torch's current stream
 unless one is given.  There is no fallback: if the built library is absent
 the import fails, and on a machine without a GPU the execute calls raise.
+
+The execute calls check their rank tensors and read their addresses in native
+code (csrc/bind.cpp); buffers that it does not take, and faults, go through
+:func:`_ptr_table` here.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
-import weakref
 from typing import Sequence
 
 import torch  # noqa: F401  (loads the HIP runtime torch was built with, before libar.so)
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libar.so")
+BIND_PATH = os.path.join(_HERE, "_arbind.so")
 
 AR_OK, AR_ERR_INVALID_ARG, AR_ERR_UNSUPPORTED, AR_ERR_ALIAS = 0, 1, 2, 3
 AR_ERR_OUT_OF_MEMORY, AR_ERR_HIP, AR_ERR_NO_DEVICE, AR_ERR_INTERNAL = 4, 5, 6, 7
@@ -131,6 +136,19 @@ def _load():
 lib = _load()
 
 
+def _load_bind():
+    if not os.path.exists(BIND_PATH):
+        raise ImportError("_arbind.so is not built (%s); run `python -m paper_2004_09362_amd.build`" % BIND_PATH)
+    spec = importlib.util.spec_from_file_location("_arbind", BIND_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.ar_execute_batched, lib.ar_execute_noalloc)))
+    return mod
+
+
+_bind_execute = _load_bind().execute
+
+
 def status_name(s: int) -> str:
     return lib.ar_status_string(int(s)).decode()
 
@@ -240,8 +258,6 @@ def ar_plan_set_path(plan: int, path: int):
 
 
 _TORCH_DTYPE = {AR_INT32: torch.int32, AR_FLOAT32: torch.float32}
-# per plan: the last call whose buffers passed the checks (see _ptr_table)
-_CHECKED: dict = {}
 
 
 def _ptr_table(plan: int, rank_buffers, batch: int = 1, instance_stride: int | None = None,
@@ -260,15 +276,7 @@ def _ptr_table(plan: int, rank_buffers, batch: int = 1, instance_stride: int | N
         st = ar_plan_stats(plan)
         info = _PLAN_INFO[plan] = (st.P, st.n, None)
     P, n, dt = info
-    # the same (live) tensor objects at the same addresses as this plan's last
-    # checked call -- what a loop of executes passes: only the addresses are
-    # re-read (weak references, so the plan keeps no buffer alive)
     addrs = [b.data_ptr() if isinstance(b, torch.Tensor) else int(b) for b in bufs]
-    key = (tuple(addrs), batch, instance_stride, _on_gpu)
-    last = _CHECKED.get(plan)
-    if last is not None and last[0] == key and len(last[1]) == len(bufs) and \
-            all(r is None or r() is b for r, b in zip(last[1], bufs)):
-        return (ctypes.c_void_p * P)(*addrs)
     if len(bufs) != P:
         raise ArError(AR_ERR_INVALID_ARG, "rank buffers", "the plan has P=%d ranks, got %d buffers" % (P, len(bufs)))
     if batch < 1:
@@ -303,7 +311,6 @@ def _ptr_table(plan: int, rank_buffers, batch: int = 1, instance_stride: int | N
                 raise ArError(AR_ERR_INVALID_ARG, "rank buffers",
                               "rank %d's tensor holds %d elements from its start, the call needs %d "
                               "((batch - 1) * instance_stride + n)" % (x, have - b.storage_offset(), extent))
-    _CHECKED[plan] = (key, [weakref.ref(b) if isinstance(b, torch.Tensor) else None for b in bufs])
     return (ctypes.c_void_p * P)(*addrs)
 
 
@@ -315,12 +322,38 @@ def _stream_handle(stream) -> int:
     return int(stream)
 
 
+def _native(plan: int, rank_buffers, batch: int, instance_stride: int, stream, which: int, where: str) -> bool:
+    """The call through csrc/bind.cpp (which: 0 ar_execute_batched, 1
+    ar_execute_noalloc); False where the Python path has to look at its
+    buffers (see there)."""
+    info = _PLAN_INFO.get(plan)
+    if info is None or not torch.cuda.is_initialized():  # no GPU tensor exists before
+        return False
+    dev = torch._C._cuda_getDevice()
+    if stream is None:
+        handle = torch._C._cuda_getCurrentRawStream(dev)
+    elif isinstance(stream, torch.cuda.Stream):
+        handle = stream.cuda_stream
+    else:
+        return False
+    st = _bind_execute(plan, info, rank_buffers, batch, instance_stride, dev, handle, which)
+    if st is None:
+        return False
+    if st != AR_OK:
+        _check(st, where)
+    return True
+
+
 def ar_execute(plan: int, rank_buffers: Sequence, stream=None):
+    if _native(plan, rank_buffers, 1, 0, stream, 0, "ar_execute"):  # one instance: any stride below n is n
+        return
     tbl = _ptr_table(plan, rank_buffers)
     _check(lib.ar_execute(plan, tbl, _stream_handle(stream)), "ar_execute")
 
 
 def ar_execute_batched(plan: int, rank_buffers: Sequence, batch: int, instance_stride: int, stream=None):
+    if _native(plan, rank_buffers, batch, instance_stride, stream, 0, "ar_execute_batched"):
+        return
     tbl = _ptr_table(plan, rank_buffers, batch, instance_stride)
     _check(lib.ar_execute_batched(plan, tbl, batch, instance_stride, _stream_handle(stream)), "ar_execute_batched")
 
@@ -328,6 +361,8 @@ def ar_execute_batched(plan: int, rank_buffers: Sequence, batch: int, instance_s
 def ar_execute_noalloc(plan: int, rank_buffers: Sequence, batch: int, instance_stride: int, stream=None):
     """ar_execute_batched that never allocates device memory (scratch from
     the library's per-device array; see include/ar.h)."""
+    if _native(plan, rank_buffers, batch, instance_stride, stream, 1, "ar_execute_noalloc"):
+        return
     tbl = _ptr_table(plan, rank_buffers, batch, instance_stride)
     _check(lib.ar_execute_noalloc(plan, tbl, batch, instance_stride, _stream_handle(stream)), "ar_execute_noalloc")
 
@@ -394,7 +429,6 @@ def ar_plan_model_time(plan: int, alpha: float, beta: float, gamma: float) -> fl
 
 def ar_plan_destroy(plan: int):
     _PLAN_INFO.pop(plan, None)
-    _CHECKED.pop(plan, None)
     lib.ar_plan_destroy(plan)
 
 

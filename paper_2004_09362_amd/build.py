@@ -22,6 +22,9 @@ SOURCES = [os.path.join(CSRC, f) for f in ["plan.cpp", "capi.cpp", "kernels.hip"
 HEADERS = [os.path.join(CSRC, f) for f in ("ar_internal.hpp", "device_common.hpp", "fused_col.hpp",
                                                "fused_free.hpp")] + [
     os.path.join(ROOT, "include", "ar.h")]
+# The native part of the Python binding: host code only, against torch's and Python's headers.
+BIND_SOURCE = os.path.join(CSRC, "bind.cpp")
+BIND_LIB = os.path.join(HERE, "_arbind.so")
 OBJDIR = os.path.join(HERE, "_build")
 GENDIR = os.path.join(OBJDIR, "gen")
 
@@ -96,6 +99,33 @@ def _compile(src: str, incremental: bool = False) -> tuple[str, str]:
     return obj, "\n".join(warn)
 
 
+def _build_bind(incremental: bool = False) -> str:
+    """Compile _arbind.so; returns the compiler's warnings."""
+    if incremental and os.path.exists(BIND_LIB):
+        t = os.path.getmtime(BIND_LIB)
+        if all(os.path.getmtime(f) <= t for f in (BIND_SOURCE, os.path.join(ROOT, "include", "ar.h"))):
+            return ""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    tmp = BIND_LIB + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
+    for p in include_paths():
+        cmd += ["-isystem", p]
+    cmd += [BIND_SOURCE, "-o", tmp, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python",
+            "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("compiling %s failed:\n%s%s" % (BIND_SOURCE, res.stdout, res.stderr))
+    os.replace(tmp, BIND_LIB)
+    return res.stderr
+
+
 def build(verbose: bool = False, incremental: bool = False) -> str:
     """Compile every source (in parallel) and link libar.so.  Rebuilds every
     unit unless ``incremental`` (then only units older than their sources)."""
@@ -106,9 +136,11 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     units = group + col_units() + [f for f in SOURCES if f not in group]
     workers = max(1, min(len(units), int(os.environ.get("MAX_JOBS", os.cpu_count() or 1))))
     with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as ex:
+        bind = ex.submit(_build_bind, incremental)
         results = list(ex.map(lambda src: _compile(src, incremental), units))
+        bind_warn = bind.result()
     if verbose:
-        for _, warn in results:
+        for _, warn in results + [("", bind_warn)]:
             if warn:
                 sys.stderr.write(warn + "\n")
     tmp = LIB + ".tmp%d" % os.getpid()
@@ -185,10 +217,11 @@ def source_hash(families) -> str:
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(BIND_LIB):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS + [os.path.abspath(__file__)])
+    return (any(os.path.getmtime(f) > t for f in SOURCES + HEADERS + [os.path.abspath(__file__)])
+            or os.path.getmtime(BIND_SOURCE) > os.path.getmtime(BIND_LIB))
 
 
 if __name__ == "__main__":

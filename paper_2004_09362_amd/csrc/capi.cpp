@@ -284,14 +284,16 @@ ar_status check_buffers(const ar_plan* pl, void* const* bufs, int64_t batch, int
   // on the stack (P <= 128): the allocation-free entry point uses this too
   std::array<std::pair<uintptr_t, int32_t>, ar::kMaxP> sorted;
   *all16 = true;
+  bool ascending = true;  // rows of one allocation: sorted already
   for (int32_t x = 0; x < P; ++x) {
     const uintptr_t p = reinterpret_cast<uintptr_t>(bufs[x]);
     if (p == 0) return fail(AR_ERR_INVALID_ARG, "rank buffer " + std::to_string(x) + " is NULL");
     if (p % 4 != 0) return fail(AR_ERR_INVALID_ARG, "rank buffer " + std::to_string(x) + " is not 4-byte aligned");
     if (p % 16 != 0) *all16 = false;
     sorted[size_t(x)] = {p, x};
+    if (x > 0 && p < sorted[size_t(x) - 1].first) ascending = false;
   }
-  std::sort(sorted.begin(), sorted.begin() + P);
+  if (!ascending) std::sort(sorted.begin(), sorted.begin() + P);
   for (size_t i = 1; i < size_t(P); ++i)
     if (extent > 0 && sorted[i].first < sorted[i - 1].first + uintptr_t(extent))
       return fail(AR_ERR_ALIAS, "rank buffers " + std::to_string(sorted[i - 1].second) + " and " +
