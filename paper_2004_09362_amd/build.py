@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libar.so")
 SOURCES = [os.path.join(CSRC, f) for f in ["plan.cpp", "capi.cpp", "kernels.hip", "fused_lo.hip", "fused_group.hip",
-                                           "fused_free.hip",
+                                           "fused_free.hip", "fused_small.hip",
                                            "broadcast.hip", "noalloc.hip"]]
 HEADERS = [os.path.join(CSRC, f) for f in ("ar_internal.hpp", "device_common.hpp", "fused_col.hpp",
                                                "fused_free.hpp")] + [
@@ -164,6 +164,7 @@ FAMILIES = {
     "col": ["fused_col.hpp"],  # and the generated units (col_unit_text)
     "group": ["fused_group.hip"],
     "free": ["fused_free.hip", "fused_free.hpp"],
+    "small": ["fused_small.hip"],
     "bcast": ["broadcast.hip"],
 }
 
@@ -175,7 +176,8 @@ def kernel_families(kernel: str) -> list[str]:
     for part in kernel.split("+"):
         for prefix, fam in (("step_kernel", "step"), ("fused_lo_kernel", "lo"), ("fused_bo_kernel", "col"),
                             ("fused_mid_kernel", "col"), ("fused_rot_kernel", "col"), ("fused_xor_kernel", "group"),
-                            ("fused_ring_kernel", "group"), ("fused_free_kernel", "free"), ("broadcast", "bcast")):
+                            ("fused_ring_kernel", "group"), ("fused_free_kernel", "free"),
+                            ("fused_small_kernel", "small"), ("broadcast", "bcast")):
             if part.startswith(prefix):
                 out.append(fam)
                 break

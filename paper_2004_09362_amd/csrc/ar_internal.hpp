@@ -264,6 +264,23 @@ int launch_fused_bo(const ColArgs& a, int dtype, int op, bool nt, int grid, void
 template <int P>
 int launch_fused_mid(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream);
 int launch_fused_col_any(const ColArgs& a, int P, int dtype, int op, bool nt, int grid, void* stream);
+// The same plans, fp32, for calls of up to kSmallCols columns at many ranks
+// (fused_small.hip): shifted plans from kSmallShiftedMinP ranks; bandwidth-
+// optimal ones, and latency-optimal ones at odd P (whose column kernel needs
+// more than a wave's 256 registers), from kSmallMinP.  In a graph of launches,
+// us, column kernel / this one, at 106 and 4096 columns: shifted P = 64 5.5 / 4.75
+// and 4.8 / 5.4, P = 80 6.5 / 5.3 and 5.9 / 6.0, P = 100 7.4 / 5.5 and 7.1 / 6.4, P = 127
+// 8.9 / 6.0 and 9.2 / 7.1; latency-optimal P = 100 4.2 / 5.25, P = 127 7.6 / 5.7 and 8.0 /
+// 6.8, P = 128 4.45 / 5.6; bandwidth-optimal (with its broadcast) P = 100 7.6 / 7.3 and
+// 8.3 / 8.3, P = 127 8.8 / 7.7 and 9.3 / 9.1; at 8192 columns all the other way round.
+constexpr int kSmallShiftedMinP = 80, kSmallMinP = 97;
+constexpr int64_t kSmallCols = 4096;
+inline bool small_call(const ColArgs& a) {
+  const bool lo = (int64_t(1) << a.r) >= a.P;
+  const bool ranks = a.r == 0 ? a.P >= kSmallMinP : lo ? a.P >= kSmallMinP && a.P % 2 == 1 : a.P >= kSmallShiftedMinP;
+  return ranks && a.n * a.instances <= kSmallCols && a.tune.nt < 0 && !a.tune.cap_forced && !a.tune.layout_forced;
+}
+int launch_fused_small(const ColArgs& a, int op, void* stream);
 // Rank-slot kernel on flat columns (batches of short blocks, sums): the
 // cyclic butterfly plans with r < L, or the Ring (ring = true); and its
 // dispatcher over P = 2..128.

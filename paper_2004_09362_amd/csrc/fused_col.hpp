@@ -368,6 +368,7 @@ int launch_rot_nt(const ColArgs& a, int op, bool ring, int grid, hipStream_t s) 
 template <int P>
 int launch_fused_rot(const ColArgs& a, int dtype, int op, bool ring, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
+  if (!ring && small_call(a)) return launch_fused_small(a, op, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   return (a.split && P < 48) || flat_on_lines(a) ? launch_rot_nt<P, true>(a, op, ring, grid, s)
                                                  : launch_rot_nt<P, false>(a, op, ring, grid, s);
@@ -494,6 +495,7 @@ int launch_wide(const ColArgs& args, int op, bool nt, hipStream_t s) {
 template <int P>
 int launch_fused_bo(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
+  if (small_call(a)) return launch_fused_small(a, op, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if constexpr (P <= kWideMaxP)
     if (wide_lanes<P>(a)) return launch_wide<P>(a, op, nt, s);
@@ -516,6 +518,7 @@ namespace ar {
 template <int P>
 int launch_fused_mid(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
+  if (small_call(a)) return launch_fused_small(a, op, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if constexpr (P <= kWideMaxP)
     if (wide_lanes<P>(a)) return launch_wide<P>(a, op, nt, s);
