@@ -201,9 +201,8 @@ typedef struct {
                                         to hbm_bytes_stepwise                            */
   int32_t fused_bcast_stream;        /* FUSED path split into two launches: 1 when the
                                         broadcast of one instance copies destination by
-                                        destination -- flat columns (short blocks), or
-                                        blocks of at least 1024 elements in rank buffers
-                                        of at least 2 MiB (AR_BCAST_STREAM overrides the
+                                        destination -- flat columns, or rank buffers of
+                                        at least 2 MiB (AR_BCAST_STREAM overrides the
                                         size rule), for rank buffers of any alignment
                                         and instances with or without gaps whose span,
                                         (batch - 1) * instance_stride + n, is below

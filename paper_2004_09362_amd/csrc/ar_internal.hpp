@@ -220,12 +220,7 @@ struct ColArgs {
   // each lane from its index i in the instance): the first m blocks hold
   // q + 1 elements (q1div = q + 1), the others q (qdiv = max(q, 1)).
   FastDiv q1div, qdiv;
-  // The call's extent, and the broadcast of a split call: copied destination
-  // by destination (dest_major) in XCD regions or interleaved, with
-  // nontemporal stores or not, on a device of `xcds` XCDs.
-  int64_t n, instances;
-  uint32_t xcds;
-  int32_t dest_major, bcast_regions, bcast_nt;
+  int64_t n, instances;  // the call's extent
   FusedTuning tune;
 };
 
@@ -293,16 +288,15 @@ int launch_fused_rot_any(const ColArgs& a, int P, int dtype, int op, bool ring, 
 int launch_fused_xor(const ColArgs& a, int P, int dtype, int op, bool nt, int grid, void* stream);
 int launch_fused_ring(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream);
 // Second half of a split fused launch (broadcast.hip): the results, stored
-// on rank 0 by the reducing kernel, copied to the other P - 1 ranks.
+// on rank 0 by the reducing kernel, copied to the other P - 1 ranks, tiled as
+// the reducing launch.
 int launch_broadcast(const ColArgs& a, int dtype, bool nt, int grid, void* stream);
 
-// The same copy ordered destination by destination (broadcast.hip), for
-// contiguous instances in 16-byte aligned rank buffers (launch_broadcast
-// does the same for other layouts).  A workgroup copies one chunk of
-// kStreamChunk consecutive columns of the batch's flat column space (the
-// byte offset in every rank buffer is 4 * column) to one destination rank,
-// one 16-byte store per thread; ids run slice by slice (C chunks per slice),
-// destination by destination, chunk by chunk.
+// The same copy ordered destination by destination (broadcast.hip), for rank
+// buffers of any alignment and instances with or without gaps.  A workgroup
+// copies one chunk of kStreamChunk consecutive columns of a rank's span to one
+// destination rank, one 16-byte store per thread; ids run slice by slice (C
+// chunks per slice), destination by destination, chunk by chunk.
 constexpr uint32_t kStreamBlock = 256;  // threads per workgroup, four columns each
 constexpr uint32_t kStreamChunk = 4 * kStreamBlock;
 // n / d without a branch: t = umulhi(n, mul), (t + ((n - t) >> s1)) >> s2;
@@ -321,25 +315,22 @@ inline uint32_t stream_div_host(uint32_t n, const StreamDiv& d) {
 }
 // The scalars come first, so that a workgroup reads them in one batch of
 // kernel-argument loads before it looks up its two rank pointers.
-struct StreamArgs {
+struct CopyArgs {
+  StreamDiv sdiv, cdiv;  // C * P, C (chunks per slice, a multiple of the XCD count X)
+  // chunk of workgroup c of a slice: (c & mask) * per_xcd + (c >> shift) --
+  // regions: X - 1, C / X, log2 X; interleaved (chunk c itself): 0, 0, 0
+  uint32_t mask, per_xcd, shift;
+  uint32_t chunks;  // chunks of the longest destination grid
+  uint32_t cols;    // columns of a rank's span: (instances - 1) * stride + n
+  uint32_t n;       // gap: instance length
   uint32_t P;
-  uint32_t cols;            // batch * n flat columns, < 2^32 - kStreamChunk
-  uint32_t n, q, m;         // instance length, n / P, n % P
-  uint32_t big;             // m * (q + 1): columns of an instance in its first m blocks (q + 1 each)
-  uint32_t flat;            // 1: the reducing launch ran on flat columns; 0: on block tiles (q >= kStreamChunk)
-  uint32_t chunks;          // ceil(cols / kStreamChunk)
-  uint32_t id0;             // id of this launch's first workgroup (a multiple of C * P)
-  uint32_t regions;         // 1: XCD x takes the x-th C / X chunks of a slice; 0: every X-th chunk
-  uint32_t xcd_shift;       // log2 of the XCD count X (a power of two; C is a multiple of X)
-  uint32_t per_xcd;         // C / X
-  uint32_t order_forced;    // 1: regions (or not) by an override, not by the size rules
-  StreamDiv ndiv, q1div, qdiv;  // n, q + 1, q
-  StreamDiv cdiv, sdiv;     // C (a multiple of the XCD count), C * P
+  StreamDiv stdiv;  // gap: the instance stride
   void* user[kMaxP];
 };
-// straddle: some block or instance boundary falls inside a chunk (block
-// tiles with n % P != 0 or n / P not a multiple of kStreamChunk).
-int launch_broadcast_stream(const StreamArgs& a, bool nt, bool straddle, uint32_t grid, void* stream);
+// nt: nontemporal loads and stores.  gap: the span holds gaps between
+// instances.  lines: each destination's chunk grid starts on a 128-byte line
+// of its buffer; otherwise on column 0.  grid: whole slices of C * P workgroups.
+int launch_copy(const CopyArgs& a, uint32_t grid, bool nt, bool gap, bool lines, void* stream);
 // Device address of the allocation-free scratch (noalloc.hip) on `device`,
 // which must be the current device; looked up on the first call per device.
 // Returns a hipError_t value.

@@ -15,7 +15,7 @@
 // (col_tile_column, device_common.hpp), or 64 consecutive flat columns per
 // wave; every wave writes the P - 1 destinations of its columns.  It serves
 // the calls the kernel below does not: rank spans under the size rule of
-// capi.cpp, and index spaces beyond 32 bits.  Loads and stores are
+// capi.cpp (copy_call), and index spaces beyond 32 bits.  Loads and stores are
 // nontemporal (NT) or ordinary: from P = 96 ranks, streaming the P - 1
 // stores nontemporally at one resident workgroup per CU was 3-4% faster, and
 // on flat columns nontemporal stores were 1-11% faster at any P; below
@@ -23,7 +23,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <cstring>
 
 #include "ar_internal.hpp"
 #include "device_common.hpp"
@@ -70,8 +69,9 @@ __global__ __launch_bounds__(kBlock) void broadcast_kernel(const ColArgs a) {
 // XCD c mod X for every destination.  The chunk it copies is chunk c
 // (interleaved: 1 MB of each slice per XCD, in 4 KB pieces X chunks apart),
 // or in XCD regions the ((c mod X) * C / X + c / X)-th (XCD x copies the x-th
-// contiguous C / X chunks: 256 KB of each slice).  With C not a multiple of
-// X the copy took 1.3x the time, and with 2 MB per XCD 1.4x.
+// contiguous C / X chunks of each slice).  With C not a multiple of X the copy
+// took 1.3x the time, and with 2 MB per XCD 1.4x.  The order and C are the
+// host's choice (copy_call, capi.cpp).
 //
 // Rank buffers need no common alignment: each destination has its own chunk
 // grid, laid on the 128-byte lines of its buffer (its first chunk starts up
@@ -98,19 +98,6 @@ __global__ __launch_bounds__(kBlock) void broadcast_kernel(const ColArgs a) {
 // words apart, and the second pointer loaded after the check, the copy took
 // 2-5% longer.)  LINES = false, every destination on a line boundary, is
 // kept for the same reason: its bounds check waits for no pointer.
-struct BcastArgs {
-  StreamDiv sdiv, cdiv;  // C * P, C (chunks per slice, a multiple of the XCD count X)
-  // chunk of workgroup c of a slice: (c & mask) * per_xcd + (c >> shift) --
-  // regions: X - 1, C / X, log2 X; interleaved (chunk c itself): 0, 0, 0
-  uint32_t mask, per_xcd, shift;
-  uint32_t chunks;  // chunks of the longest destination grid
-  uint32_t cols;    // columns of a rank's span: (instances - 1) * stride + n
-  uint32_t n;       // GAP: instance length
-  uint32_t P;
-  StreamDiv stdiv;  // GAP: the instance stride
-  void* user[kMaxP];
-};
-
 __device__ __forceinline__ uint32_t sdiv(uint32_t n, const StreamDiv& d) {
   const uint32_t t = __umulhi(n, d.mul);
   return (t + ((n - t) >> d.s1)) >> d.s2;
@@ -122,7 +109,7 @@ typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // LINES: the chunk grid of a destination starts on a 128-byte line of its
 // buffer; else on column 0.
 template <bool NT, bool GAP, bool LINES>
-__global__ __launch_bounds__(kStreamBlock) void broadcast_stream_kernel(const BcastArgs a) {
+__global__ __launch_bounds__(kStreamBlock) void broadcast_stream_kernel(const CopyArgs a) {
   const uint32_t id = blockIdx.x;
   const uint32_t s = sdiv(id, a.sdiv);
   const uint32_t r = id - s * a.sdiv.d;
@@ -186,7 +173,10 @@ __global__ __launch_bounds__(kStreamBlock) void broadcast_stream_kernel(const Bc
 // way or slower with it.
 constexpr uint32_t kCopyLds = 39 * 1024;
 
-void launch_copy(const BcastArgs& a, uint32_t grid, bool nt, bool gap, bool lines, hipStream_t s) {
+}  // namespace
+
+int launch_copy(const CopyArgs& a, uint32_t grid, bool nt, bool gap, bool lines, void* stream) {
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const dim3 g(grid), blk(kStreamBlock);
   const uint32_t lds = a.mask != 0 && !gap ? kCopyLds : 0;
 #define AR_COPY(GAP, LINES)                                                                               \
@@ -198,94 +188,11 @@ void launch_copy(const BcastArgs& a, uint32_t grid, bool nt, bool gap, bool line
   else if (lines) AR_COPY(false, true);
   else AR_COPY(false, false);
 #undef AR_COPY
-}
-
-// Launches the destination-major copy over a filled-in span, or returns
-// false when its grid would reach 2^32 work-items.  The slices of a call are
-// evened out and rounded up to the XCD count (a short last slice in regions
-// leaves most XCDs idle): at most 1 MB per XCD interleaved, 256 KB in regions
-// (at 8-32 MB per rank 1 MB regions ran 3-50% slower; from 64 MB the sizes ran
-// within a few percent).
-bool launch_dest_major(BcastArgs& a, uint32_t xcds, bool regions, bool gap, bool nt, hipStream_t s) {
-  uint32_t shift = 0;
-  while ((1u << shift) < xcds) ++shift;
-  const bool reg = regions && (1u << shift) == xcds;
-  bool lines = false;
-  for (uint32_t x = 1; x < a.P; ++x) lines |= reinterpret_cast<uintptr_t>(a.user[x]) % 128 != 0;
-  const uint64_t chunks = (uint64_t(a.cols) + (lines ? 31 : 0) + kStreamChunk - 1) / kStreamChunk;
-  const uint64_t cmax = (reg ? 64u : 256u) * xcds;
-  const uint64_t slices = (chunks + cmax - 1) / cmax;
-  const uint64_t C = ((chunks + slices - 1) / slices + xcds - 1) / xcds * xcds;
-  const uint64_t grid = (chunks + C - 1) / C * C * a.P;
-  if (grid > uint64_t(UINT32_MAX) / kStreamBlock) return false;
-  a.chunks = uint32_t(chunks);
-  a.cdiv = stream_div(uint32_t(C));
-  a.sdiv = stream_div(uint32_t(C) * a.P);
-  a.mask = reg ? xcds - 1 : 0;
-  a.shift = reg ? shift : 0;
-  a.per_xcd = reg ? uint32_t(C) / xcds : 0;
-  launch_copy(a, uint32_t(grid), nt, gap, lines, s);
-  return true;
-}
-
-}  // namespace
-
-constexpr int64_t kCopyRegionsMinBytes = int64_t(16) << 20;
-
-int launch_broadcast_stream(const StreamArgs& a, bool nt, bool /*straddle*/, uint32_t grid, void* stream) {
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  BcastArgs b;
-  std::memset(&b, 0, sizeof b);
-  b.P = a.P;
-  b.cols = a.cols;
-  b.n = a.n;
-  b.stdiv = StreamDiv{1, 0, 0, 0};
-  std::memcpy(b.user, a.user, sizeof b.user);
-  // every source on rank 0's row, the order no longer depends on the blocks:
-  // unless it is forced, regions above kCopyRegionsMinBytes per rank, whose
-  // slices then fill the chip (P = 127 at 256 MB: 4.67-4.70 ms against
-  // 4.89-4.96 interleaved; at 18 MB 0.347-0.351 against 0.350-0.355, at 4.5 MB
-  // 0.092 against 0.084)
-  const bool regions = a.order_forced ? a.regions != 0 : int64_t(a.cols) * 4 > kCopyRegionsMinBytes;
-  if (!launch_dest_major(b, 1u << a.xcd_shift, regions, false, nt, s)) {
-    // a grid just below 2^32 work-items that the line-aligned grids' extra
-    // chunk takes past it: the common grid
-    b.chunks = a.chunks;
-    b.cdiv = a.cdiv;
-    b.sdiv = a.sdiv;
-    b.mask = a.regions ? (1u << a.xcd_shift) - 1 : 0;
-    b.shift = a.regions ? a.xcd_shift : 0;
-    b.per_xcd = a.regions ? a.per_xcd : 0;
-    launch_copy(b, grid, nt, false, false, s);
-  }
   return int(hipGetLastError());
 }
 
-// Rank buffers off 16-byte boundaries, or gaps between the instances: the
-// destination-major copy too wherever the size rule of capi.cpp asks for it
-// (a.dest_major) and a rank's span fits its 32-bit positions.  With gaps,
-// instances that start off 32-byte sectors (a stride that is no multiple of
-// 8) or hold fewer than 512 elements take cached stores, which leave the
-// parts of a line that different workgroups write to meet in L2, in
-// interleaved order: P = 37, 65536 x 106, stride 113: 3.1 TB/s against 2.0
-// nontemporal; P = 64, 8192 x 2304, stride 2311: 5.75 against 5.55; strides
-// 2328 and 1024 the other way round, 5.5 against 6.2 and 5.25 against 6.0.
 int launch_broadcast(const ColArgs& a, int dtype, bool nt, int grid, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const int64_t span = (a.instances - 1) * a.stride + a.n;
-  if (a.dest_major && span <= int64_t(UINT32_MAX) - 2 * kStreamChunk) {
-    const bool gap = a.instances > 1 && a.stride != a.n;
-    BcastArgs b;
-    std::memset(&b, 0, sizeof b);
-    b.P = uint32_t(a.P);
-    b.cols = uint32_t(span);
-    b.n = uint32_t(a.n);
-    b.stdiv = stream_div(gap ? uint32_t(a.stride) : 1u);
-    std::memcpy(b.user, a.user, sizeof b.user);
-    const bool sectors = !gap || (a.stride % 8 == 0 && a.n >= 512);
-    if (launch_dest_major(b, a.xcds, a.bcast_regions != 0 && sectors, gap, a.bcast_nt != 0 && sectors, s))
-      return int(hipGetLastError());
-  }
   const dim3 g(grid), blk(kBlock);
   if (dtype == 0) {
     if (nt) hipLaunchKernelGGL((broadcast_kernel<int32_t, true>), g, blk, a.lds, s, a);

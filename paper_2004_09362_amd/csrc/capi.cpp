@@ -58,33 +58,33 @@ constexpr int32_t kFlatSplitMinP = 33;
 // CU: 3-4% faster at P = 100-128 than cached stores at two workgroups per CU,
 // the same at P = 64, and 13% slower at P = 48.  Neither change helps alone.
 constexpr int32_t kBcastStreamMinP = 96;
-// The destination-major broadcast (broadcast.hip) by default: on flat
-// columns at any P, and on block tiles where a rank's span of the call
-// reaches kBcastStreamMinBytes (smaller spans not measured).  Measured
-// against the tiled copy (rank rows back to back), it took 6-24% less time
-// on block tiles at P = 64-128 and 2-256 MB per rank (5.7-7.2 TB/s against
-// 5.0-6.2), and 6-21% less on flat columns at P = 37-128 and 4.5-72 MB per
-// rank.  Its chunk order: XCD regions on flat columns above
-// kBcastFlatInterleaveMaxBytes per rank (interleaved up to it, where short
-// slices left XCDs idle, and at exactly 16 MiB, two full slices, 1-5% less
-// time than regions at P = 37-127; regions 1-4% less at 20, 28 and 32 MiB,
-// within 2% either way at 24 MiB and above), and on block tiles whose
-// blocks all start on the chunk grid from kBcastRegionMinP ranks or from
-// kBcastAlignedRegionMinBytes per rank (P = 128 at 8-32 MiB: 35-38% less
-// time than interleaved; P = 64 at 32-256 MiB and P = 32 at 64 MiB: 3-5%
-// less; P = 16-64 at 8-16 MiB: 1-8% more, so interleaved there); with
-// straddling chunks interleaved below kBcastRegionMinP ranks (P = 100:
-// 5-10% less time than regions) or from kBcastInterleaveMinBytes per rank
-// (P = 127 at 256 MB: 5%), and regions otherwise, where the interleaved
-// chunks read their sources from L2 no more (P = 127 below 256 MB per rank:
-// 1.1-2.0x the time of regions).  (The block-tile figures are those of a
-// copy whose sources lay on every block's own rank; with every source on
-// rank 0, launch_broadcast_stream applies the flat rule to them too.)
+// The destination-major copy (broadcast.hip) by default: on flat columns at
+// any P, and on block tiles where a rank's span of the call reaches
+// kBcastStreamMinBytes (smaller spans not measured).  Measured against the
+// tiled copy (rank rows back to back), it took 6-24% less time on block tiles
+// at P = 64-128 and 2-256 MB per rank (5.7-7.2 TB/s against 5.0-6.2), and
+// 6-21% less on flat columns at P = 37-128 and 4.5-72 MB per rank.
 constexpr int64_t kBcastStreamMinBytes = int64_t(2) << 20;
-constexpr int64_t kBcastFlatInterleaveMaxBytes = int64_t(16) << 20;
-constexpr int64_t kBcastInterleaveMinBytes = int64_t(256) << 20;
-constexpr int64_t kBcastAlignedRegionMinBytes = int64_t(32) << 20;
-constexpr int32_t kBcastRegionMinP = 104;
+// Its chunk order, for rows of any alignment: XCD regions above
+// kCopyRegionsMinBytes per rank, whose slices then fill the chip, and
+// interleaved chunks up to it.  Every source lies on rank 0's row, so the
+// order depends on neither the blocks nor the tiles of the reducing launch.  A
+// slice holds at most kCopyInterleavedChunks chunks per XCD (1 MB),
+// interleaved, or kCopyRegionChunks (512 KB) in regions.  Whole calls, us,
+// 1 MB interleaved / regions of 256 KB / of 512 KB / of 1 MB:
+//   P = 24, 40 MiB per rank 303 / 313 / 304 / 305, 64 MiB 508 / 496 / 485 / 486;
+//   P = 33, 64 MiB 690 / 661 / 654 / 656; P = 64, 64 MiB 1337 / 1271 / 1261 / 1262;
+//   P = 127, 24 MiB 956 / 949 / 937 / 938, 64 MiB 2558 / 2456 / 2465 / 2470;
+//   rows off the lines, P = 24, 64 MiB 559 / 571 / 554 / 556;
+//   at 16 MiB P = 24 126 / 133 / 127 / 127, P = 127 619 / 635 / 619 / 620; at 8 MiB
+//   P = 17-127 regions took 0-3% longer.
+// From kCopyLargeMinP ranks and kCopyLargeMinBytes per rank regions of 256 KB:
+// P = 127 at 140 MiB 5339 against 5378, at 250 MiB 9797 against 9895 (P = 64 at
+// 250 MiB even, P = 100 0.1-0.5% less).
+constexpr int64_t kCopyRegionsMinBytes = int64_t(16) << 20;
+constexpr uint32_t kCopyInterleavedChunks = 256, kCopyRegionChunks = 128, kCopyLargeRegionChunks = 64;
+constexpr int32_t kCopyLargeMinP = 100;
+constexpr int64_t kCopyLargeMinBytes = int64_t(128) << 20;
 // Blocks of at most this many elements (many small instances) are packed:
 // a column-fused wave takes one block of 64 / max_len instances instead of 64
 // columns of one block of one instance, laid on 256-byte boundaries (which
@@ -182,8 +182,7 @@ struct ar_plan {
   // AR_BCAST_STREAM = 0|1|2|3 (the broadcast tiled by block / destination by
   // destination wherever the call allows it, with the chunk order by size,
   // interleaved, or in XCD regions; default by the size rules at
-  // kBcastStreamMinBytes, kBcastFlatInterleaveMaxBytes, kBcastInterleaveMinBytes,
-  // kBcastAlignedRegionMinBytes and kBcastRegionMinP),
+  // kBcastStreamMinBytes and kCopyRegionsMinBytes),
   // AR_FUSED_PACKED = 0|1 (column tiles of one block of one instance / of
   // several instances, for blocks of up to 64 elements; default: packed for
   // batches whose blocks hold up to kPackMaxLen elements), AR_FUSED_ROTATE =
@@ -367,11 +366,10 @@ uint32_t cap_lds(int32_t cap, int device) {
   return uint32_t(bytes);
 }
 
-// Chunks per slice of the destination-major broadcast on `device`: 256
-// chunks (1 MB) per XCD, times the XCD count, taken as the CU count over the
-// 32 CUs of a gfx950 XCD (8 on a whole MI355X, fewer on a partition).  The
-// CU count is cached per device like the LDS sizes above.
-uint32_t stream_slice_chunks(int device) {
+// XCDs of `device`: the CU count over the 32 CUs of a gfx950 XCD (8 on a whole
+// MI355X, fewer on a partition).  The CU count is cached per device like the
+// LDS sizes above.
+uint32_t xcd_count(int device) {
   static std::atomic<int32_t> cus[64];
   int32_t c = (device >= 0 && device < 64) ? cus[device].load(std::memory_order_acquire) : 0;
   if (c == 0) {
@@ -383,57 +381,84 @@ uint32_t stream_slice_chunks(int device) {
     c = v;
     if (device >= 0 && device < 64) cus[device].store(c, std::memory_order_release);
   }
-  return 256u * uint32_t(std::max<int32_t>(1, c / 32));
+  return uint32_t(std::max<int32_t>(1, c / 32));
 }
 
-// Arguments of the destination-major broadcast (broadcast.hip) when the
-// call allows it: instances contiguous (batch 1 or stride n), every rank
-// buffer 16-byte aligned, the column space and the grid within 32-bit
-// counts, and on block tiles blocks of at least kStreamChunk elements (a
-// chunk then spans at most two roots).  False: the tiled broadcast runs.
-bool stream_bcast_args(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stride, bool flat, bool regions,
-                       int device, ar::StreamArgs* sa) {
-  const ar::Schedule& s = pl->s;
-  if (batch > 1 && stride != s.n) return false;
-  const int64_t cols = batch * s.n;
-  if (cols < 1 || cols > int64_t(UINT32_MAX) - ar::kStreamChunk) return false;
-  if (!flat && s.n / s.P < int64_t(ar::kStreamChunk)) return false;
-  for (int32_t x = 0; x < s.P; ++x)
-    if (reinterpret_cast<uintptr_t>(bufs[x]) % 16 != 0) return false;
-  // chunks per slice: at most 1 MB per XCD interleaved, 256 KB per XCD in
-  // regions (at 8-32 MB per rank 1 MB regions ran 3-50% slower; from 64 MB
-  // the sizes ran within a few percent), evened out over the slices and
-  // rounded up to the XCD count, so that the last slice is about as full as
-  // the others (a short last slice in regions leaves most XCDs idle)
-  const uint32_t xcds = stream_slice_chunks(device) / 256;
+struct CopyCall {
+  ar::CopyArgs a;
+  uint32_t grid;
+  bool nt, gap, lines;
+};
+
+// The destination-major copy (broadcast.hip) of a split call, where the size
+// rule or an override asks for it and its 32-bit positions hold a rank's span;
+// false: the tiled copy runs.
+//
+// With gaps between the instances, ones that start off 32-byte sectors (a
+// stride that is no multiple of 8) or hold fewer than 512 elements take cached
+// stores, which leave the parts of a line that different workgroups write to
+// meet in L2, in interleaved order: P = 37, 65536 x 106, stride 113: 3.1 TB/s
+// against 2.0 nontemporal; P = 64, 8192 x 2304, stride 2311: 5.75 against 5.55;
+// strides 2328 and 1024 the other way round, 5.5 against 6.2 and 5.25 against
+// 6.0.
+bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stride, bool flat, int device,
+               CopyCall* c) {
+  const int32_t P = pl->s.P;
+  const int64_t n = pl->s.n, span = (batch - 1) * stride + n;
+  const int32_t mode = pl->bcast_stream_mode;
+  if (mode == 0 || (mode < 0 && !flat && span * 4 < kBcastStreamMinBytes)) return false;
+  if (span > int64_t(UINT32_MAX) - 2 * int64_t(ar::kStreamChunk)) return false;
+  const bool gap = batch > 1 && stride != n;
+  const bool sectors = !gap || (stride % 8 == 0 && n >= 512);
+  const uint32_t xcds = xcd_count(device);
   uint32_t shift = 0;
   while ((1u << shift) < xcds) ++shift;
-  const bool reg = regions && (1u << shift) == xcds;
-  const uint32_t chunks = uint32_t((cols + ar::kStreamChunk - 1) / ar::kStreamChunk);
-  const uint32_t cmax = (reg ? 64u : 256u) * xcds;
-  const uint32_t slices = (chunks + cmax - 1) / cmax;
-  const uint32_t C = ((chunks + slices - 1) / slices + xcds - 1) / xcds * xcds;
-  const int64_t grid = (int64_t(chunks) + C - 1) / C * C * s.P;
-  if (grid > int64_t(UINT32_MAX) / ar::kStreamBlock) return false;  // work-items per launch below 2^32
-  std::memset(sa, 0, sizeof *sa);
-  for (int32_t x = 0; x < s.P; ++x) sa->user[x] = bufs[x];
-  sa->P = uint32_t(s.P);
-  sa->cols = uint32_t(cols);
-  sa->n = uint32_t(s.n);
-  sa->q = uint32_t(s.n / s.P);
-  sa->m = uint32_t(s.n % s.P);
-  sa->big = sa->m * (sa->q + 1);
-  sa->flat = flat ? 1 : 0;
-  sa->ndiv = ar::stream_div(uint32_t(s.n));
-  sa->q1div = ar::stream_div(sa->q + 1);
-  sa->qdiv = ar::stream_div(std::max<uint32_t>(sa->q, 1));
-  sa->cdiv = ar::stream_div(C);
-  sa->sdiv = ar::stream_div(C * uint32_t(s.P));
-  sa->chunks = chunks;
-  sa->id0 = 0;
-  sa->regions = reg ? 1 : 0;
-  sa->xcd_shift = shift;
-  sa->per_xcd = C / xcds;
+  const bool want_regions = mode == 2 || mode == 3 ? mode == 3 : span * 4 > kCopyRegionsMinBytes;
+  const bool regions = want_regions && sectors && (1u << shift) == xcds;
+  // nontemporal at any P for calls of kFusedNtThresholdBytes and more: alone,
+  // cached stores were up to 6% faster on some shapes (P = 64 at 16 MB per
+  // rank, flat columns), but the pair then took 0.3-10% longer: the next
+  // reducing launch pays for the cached lines (P = 32-128, 4-256 MB per rank)
+  const bool want_nt = pl->bcast_nt_mode == 1 ||
+                       (pl->bcast_nt_mode < 0 && int64_t(P) * n * batch * 4 >= kFusedNtThresholdBytes);
+  std::memset(c, 0, sizeof *c);
+  for (int32_t x = 0; x < P; ++x) {
+    c->a.user[x] = bufs[x];
+    if (x > 0 && reinterpret_cast<uintptr_t>(bufs[x]) % 128 != 0) c->lines = true;
+  }
+  c->lines = c->lines || gap;
+  // The slices of a call are evened out and rounded up to the XCD count: a
+  // short last slice in regions leaves most XCDs idle.
+  const uint64_t per_xcd = !regions ? kCopyInterleavedChunks
+                           : P >= kCopyLargeMinP && span * 4 >= kCopyLargeMinBytes ? kCopyLargeRegionChunks
+                                                                                   : kCopyRegionChunks;
+  const uint64_t cmax = per_xcd * xcds;
+  uint64_t chunks, C, grid;
+  for (;; c->lines = false) {
+    chunks = (uint64_t(span) + (c->lines ? 31 : 0) + ar::kStreamChunk - 1) / ar::kStreamChunk;
+    const uint64_t slices = (chunks + cmax - 1) / cmax;
+    C = ((chunks + slices - 1) / slices + xcds - 1) / xcds * xcds;
+    grid = (chunks + C - 1) / C * C * uint64_t(P);
+    if (grid <= uint64_t(UINT32_MAX) / ar::kStreamBlock) break;  // work-items per launch below 2^32
+    // without gaps, the common grid may still fit where the lead of up to 31
+    // columns takes the line grids one chunk too far
+    if (!c->lines || gap) return false;
+  }
+  c->grid = uint32_t(grid);
+  c->gap = gap;
+  c->nt = want_nt && sectors;
+  c->a.P = uint32_t(P);
+  c->a.cols = uint32_t(span);
+  c->a.n = uint32_t(n);
+  c->a.stdiv = ar::stream_div(gap ? uint32_t(stride) : 1u);
+  c->a.chunks = uint32_t(chunks);
+  c->a.cdiv = ar::stream_div(uint32_t(C));
+  c->a.sdiv = ar::stream_div(uint32_t(C) * uint32_t(P));
+  if (regions) {
+    c->a.mask = xcds - 1;
+    c->a.shift = shift;
+    c->a.per_xcd = uint32_t(C) / xcds;
+  }
   return true;
 }
 
@@ -668,39 +693,16 @@ ar_status run_fused_col(ar_plan* pl, void* const* bufs, int64_t batch, int64_t s
   if (e != 0) return hip_fail(hipError_t(e), "column-fused kernel launch");
   if (tm) tm->mark();
   if (pl->fused_split) {
-    // the tiled copy: nontemporal stores from kBcastStreamMinP ranks up, and
-    // on flat columns at any P (P = 37: 11% faster, P = 48-128: 1-3%)
-    const bool big = int64_t(s.P) * s.n * batch * 4 >= kFusedNtThresholdBytes;
-    const bool bnt = pl->bcast_nt_mode == 1 ||
-                     (pl->bcast_nt_mode < 0 && (s.P >= kBcastStreamMinP || flat_short) && big);
-    ar::StreamArgs sa;
-    const int64_t span = batch * s.n * 4;
-    const bool want_stream =
-        pl->bcast_stream_mode >= 1 || (pl->bcast_stream_mode < 0 && (a.flat || span >= kBcastStreamMinBytes));
-    // chunks can straddle two blocks when a block or instance boundary is
-    // not a multiple of the chunk
-    const bool straddle = !a.flat && (s.n % s.P != 0 || (s.n / s.P) % ar::kStreamChunk != 0);
-    bool regions;
-    if (pl->bcast_stream_mode == 2 || pl->bcast_stream_mode == 3) regions = pl->bcast_stream_mode == 3;
-    else if (a.flat) regions = span > kBcastFlatInterleaveMaxBytes;
-    else if (!straddle) regions = s.P >= kBcastRegionMinP || span >= kBcastAlignedRegionMinBytes;
-    else regions = s.P >= kBcastRegionMinP && span < kBcastInterleaveMinBytes;
-    // the destination-major copy: nontemporal at any P (launches of
-    // kFusedNtThresholdBytes and more).  Alone, its cached stores were up
-    // to 6% faster on some shapes (P = 64 at 16 MB per rank, flat columns),
-    // but the pair then took 0.3-10% longer: the next reducing launch pays
-    // for the cached lines (P = 32-128, 4-256 MB per rank, flat and block)
-    const bool snt = pl->bcast_nt_mode == 1 || (pl->bcast_nt_mode < 0 && big);
-    if (want_stream && stream_bcast_args(pl, bufs, batch, stride, a.flat != 0, regions, device, &sa)) {
-      sa.order_forced = pl->bcast_stream_mode >= 2 ? 1 : 0;
-      const uint32_t sgrid = (sa.chunks + sa.cdiv.d - 1) / sa.cdiv.d * sa.sdiv.d;
-      e = ar::launch_broadcast_stream(sa, snt, straddle, sgrid, stream);
+    CopyCall c;
+    if (copy_call(pl, bufs, batch, stride, a.flat != 0, device, &c)) {
+      e = ar::launch_copy(c.a, c.grid, c.nt, c.gap, c.lines, stream);
     } else {
+      // the tiled copy: nontemporal stores from kBcastStreamMinP ranks up, and
+      // on flat columns at any P (P = 37: 11% faster, P = 48-128: 1-3%)
+      const bool big = int64_t(s.P) * s.n * batch * 4 >= kFusedNtThresholdBytes;
+      const bool bnt = pl->bcast_nt_mode == 1 ||
+                       (pl->bcast_nt_mode < 0 && (s.P >= kBcastStreamMinP || flat_short) && big);
       a.lds = cap_lds(pl->bcast_cap, device);
-      a.xcds = stream_slice_chunks(device) / 256;
-      a.dest_major = want_stream ? 1 : 0;
-      a.bcast_regions = regions ? 1 : 0;
-      a.bcast_nt = snt ? 1 : 0;
       e = ar::launch_broadcast(a, pl->dtype, bnt, grid, stream);
     }
     if (e != 0) return hip_fail(hipError_t(e), "broadcast kernel launch");
@@ -1058,16 +1060,11 @@ ar_status ar_plan_stats(const ar_plan* plan, ar_stats* out) {
                                      : AR_PATH_STEPWISE;
   out->hbm_bytes_algorithmic = out->hbm_bytes_stepwise;
   {
-    // the default choice for one instance (ar.h): flat columns, and blocks
-    // of at least kStreamChunk elements in rank buffers of at least
-    // kBcastStreamMinBytes
-    const bool flat = plan->fused_flat;
-    const bool allowed = flat || s.n / std::max<int32_t>(s.P, 1) >= int64_t(ar::kStreamChunk);
-    const bool by_size = flat || s.n * 4 >= kBcastStreamMinBytes;
+    // the default choice for one instance (ar.h): flat columns, or rank
+    // buffers of at least kBcastStreamMinBytes
+    const bool by_size = plan->fused_flat || s.n * 4 >= kBcastStreamMinBytes;
     out->fused_bcast_stream =
-        s.P > 1 && plan->fused_split && allowed && (plan->bcast_stream_mode >= 1 || (plan->bcast_stream_mode < 0 && by_size))
-            ? 1
-            : 0;
+        s.P > 1 && plan->fused_split && (plan->bcast_stream_mode >= 1 || (plan->bcast_stream_mode < 0 && by_size)) ? 1 : 0;
   }
   return AR_OK;
 }

@@ -56,6 +56,7 @@ thread_local bool malloc_fails = false;
 thread_local bool capturing = false;  // every stream reports an active graph capture
 thread_local int launch_error = 0;  // hipError_t value every launcher returns when set
 thread_local int last_regions = -1;  // XCD-region order of the last destination-major broadcast
+thread_local int last_nt = -1;       // its nontemporal accesses
 thread_local int64_t live_allocs = 0, total_allocs = 0;
 std::atomic<uintptr_t> next_addr{uintptr_t(1) << 44};
 thread_local hipError_t last = hipSuccess;
@@ -224,38 +225,47 @@ int launch_broadcast(const ColArgs& a, int, bool, int grid, void*) {
   if (!a.split) fake::problem("broadcast without a split reduce", a.P);
   return record("broadcast", a.P, grid, a.total_tiles);
 }
-// The destination-major broadcast: every rank pointer 16-byte aligned, the
-// column space and the chunk count consistent, a chunk spanning at most two
-// roots (flat columns, or blocks of at least kStreamChunk elements), slices
-// of a multiple of 8 chunks (the fake device's 256 CUs: 8 XCDs), 2048 or
-// all the chunks, and a grid of whole slices below 2^32 work-items.
-int launch_broadcast_stream(const StreamArgs& a, bool, bool straddle, uint32_t grid, void*) {
+// The destination-major copy: rank pointers of any 4-byte alignment, the
+// column space and the chunk count consistent, destination grids on the lines
+// wherever some destination starts off one or instances have gaps, slices of a
+// multiple of 8 chunks (the fake device's 256 CUs: 8 XCDs) evened out over the
+// call, each slice's workgroups a permutation of its chunks, and a grid of
+// whole slices below 2^32 work-items.
+int launch_copy(const CopyArgs& a, uint32_t grid, bool nt, bool gap, bool lines, void*) {
   const int P = int(a.P);
-  if (P < 2 || P > kMaxP) fake::problem("stream broadcast P", P);
-  for (int x = 0; x < P && x < kMaxP; ++x)
-    if (a.user[x] == nullptr || reinterpret_cast<uintptr_t>(a.user[x]) % 16 != 0)
-      fake::problem("stream broadcast rank pointer null or not 16-byte aligned", P);
-  if (a.cols == 0 || uint64_t(a.cols) + kStreamChunk > UINT32_MAX) fake::problem("stream column count", P);
-  if (a.chunks != (a.cols + kStreamChunk - 1) / kStreamChunk) fake::problem("stream chunk count", P);
-  if (!a.flat && a.q < kStreamChunk) fake::problem("stream blocks shorter than a chunk", P);
-  if (a.n == 0 || a.cols % a.n != 0 || a.ndiv.d != a.n) fake::problem("stream instance length", P);
-  if (a.q != a.n / a.P || a.m != a.n % a.P || a.q1div.d != a.q + 1) fake::problem("stream block sizes", P);
-  const uint32_t cmax = a.regions ? 512 : 2048;  // 256 KB / 1 MB per XCD and slice, 8 XCDs
-  const uint32_t slices = (a.chunks + a.cdiv.d - 1) / std::max<uint32_t>(a.cdiv.d, 1);
-  if (a.cdiv.d % 8 != 0 || a.cdiv.d > cmax || slices != (a.chunks + cmax - 1) / cmax ||
-      uint64_t(a.cdiv.d) * slices >= uint64_t(a.chunks) + 8 * slices || a.sdiv.d != a.cdiv.d * a.P)
-    fake::problem("stream slice size", P);
-  if (a.id0 != 0 || grid != (a.chunks + a.cdiv.d - 1) / a.cdiv.d * a.sdiv.d) fake::problem("stream grid", P);
-  if (a.regions > 1 || a.xcd_shift != 3 || a.per_xcd * 8 != a.cdiv.d) fake::problem("stream XCD regions", P);
-  fake::last_regions = int(a.regions);
-  {
-    // a chunk can straddle two blocks exactly when some block or instance boundary is off the chunk grid
-    bool off_grid = false;
-    if (!a.flat)
-      for (uint32_t b = 1; b <= a.P && !off_grid; ++b) off_grid = (b * a.q + std::min(b, a.m)) % kStreamChunk != 0;
-    if (straddle != off_grid) fake::problem("stream straddle flag", P);
+  if (P < 2 || P > kMaxP) fake::problem("copy P", P);
+  bool off = false;
+  for (int x = 0; x < P && x < kMaxP; ++x) {
+    if (a.user[x] == nullptr || reinterpret_cast<uintptr_t>(a.user[x]) % 4 != 0)
+      fake::problem("copy rank pointer null or not 4-byte aligned", P);
+    if (x > 0 && reinterpret_cast<uintptr_t>(a.user[x]) % 128 != 0) off = true;
   }
-  if (uint64_t(grid) * 256 > UINT32_MAX) fake::problem("stream grid beyond 2^32 work-items", P);
+  if (a.cols == 0 || uint64_t(a.cols) + 2 * kStreamChunk > UINT32_MAX) fake::problem("copy column count", P);
+  if (a.chunks != (uint64_t(a.cols) + (lines ? 31 : 0) + kStreamChunk - 1) / kStreamChunk) fake::problem("copy chunk count", P);
+  if (gap ? !lines || a.n == 0 || a.stdiv.d <= a.n || a.cols < a.n || (a.cols - a.n) % a.stdiv.d != 0 : a.cols % a.n != 0)
+    fake::problem("copy instances", P);
+  const uint32_t C = std::max<uint32_t>(a.cdiv.d, 1), slices = (a.chunks + C - 1) / C;
+  const uint32_t most = a.mask == 0 ? 2048 : 1024;  // 1 MB per XCD interleaved, 512 KB in regions
+  if (C % 8 != 0 || C > most || uint64_t(C) * slices >= uint64_t(a.chunks) + 8 * slices || a.sdiv.d != C * a.P)
+    fake::problem("copy slice size", P);
+  if (grid != slices * C * a.P) fake::problem("copy grid", P);
+  if (uint64_t(grid) * 256 > UINT32_MAX) fake::problem("copy grid beyond 2^32 work-items", P);
+  // the common grid only where every destination is on a line, or the line grids do not fit
+  if (!lines && off && (uint64_t(a.chunks) + 1 + 7) / 8 * 8 * a.P * 256 <= UINT32_MAX - 2048ull * 256 * a.P)
+    fake::problem("copy off the lines on the common grid", P);
+  if (a.mask != 0 ? a.mask != 7 || a.shift != 3 || a.per_xcd * 8 != C : a.shift != 0 || a.per_xcd != 0)
+    fake::problem("copy XCD regions", P);
+  std::vector<bool> seen(C, false);
+  for (uint32_t c = 0; c < C; ++c) {
+    const uint32_t k = (c & a.mask) * a.per_xcd + (c >> a.shift);
+    if (k >= C || seen[k]) {
+      fake::problem("a chunk of a slice copied twice", P);
+      break;
+    }
+    seen[k] = true;
+  }
+  fake::last_regions = a.mask != 0 ? 1 : 0;
+  fake::last_nt = nt ? 1 : 0;
   return record("broadcast_stream", P, int(grid), a.chunks);
 }
 int launch_fused_lo(const FusedArgs& a, int P, int, int, int mode, bool, int grid, void*) {
@@ -491,15 +501,15 @@ static void exercise(int P, int64_t n, int k, int group, int sched, int dtype, i
   EXPECT(fake::live_allocs == 0, "%s: scratch not freed (%lld live)", what, (long long)fake::live_allocs);
 }
 
-// Which broadcast a split plan takes: the destination-major one for
-// contiguous instances in 16-byte aligned buffers, on flat columns at any P
-// or on blocks of at least kStreamChunk elements in rank spans of at least
-// 2 MiB; the tiled one otherwise.  On flat columns its chunks go in XCD
-// regions above 16 MiB per rank, interleaved up to it.
+// Which copy a split plan takes: the destination-major one for rows of any
+// alignment, on flat columns at any P or in rank spans of at least 2 MiB; the
+// tiled one otherwise and where the 32-bit grid does not hold the call.  Its
+// chunks go in XCD regions above 16 MiB per rank, interleaved up to it, by the
+// span alone: whatever the rows' alignment, the blocks and the tiles.
 struct BcastCase {
   int P;
   int64_t n;
-  int k, group, batch;
+  int k, group, batch;  // group -1: the Ring
   int64_t stride_extra;
   uintptr_t misalign;
   const char* expect;
@@ -510,12 +520,17 @@ static void check_broadcast_case(const BcastCase& c);
 
 static void broadcast_choice() {
   const BcastCase cases[] = {
-      {127, int64_t(1) << 26, 14, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 0},
+      {127, int64_t(1) << 26, 14, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 1},   // block tiles, 256 MiB per rank
+      {24, int64_t(1) << 24, 10, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 1},    // block tiles, straddling, 64 MiB
+      {24, int64_t(1) << 24, 10, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 1},    // the same, a row off 16 bytes
+      {24, int64_t(1) << 24, 46, -1, 1, 0, 4, "broadcast_stream", 1},                 // the Ring
       {127, int64_t(1) << 25, 14, AR_GROUP_CYCLIC, 2, 0, 0, "broadcast_stream", 1},   // rank slots below 256 MiB per instance: flat, regions
       {37, int64_t(1) << 22, 12, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 0},    // flat, exactly 16 MiB: interleaved
       {37, (int64_t(1) << 22) + 1024, 12, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 1},  // just above: regions
-      {127, int64_t(1) << 26, 14, AR_GROUP_CYCLIC, 3, 5, 0, "broadcast", -1},          // gaps between instances
-      {127, int64_t(1) << 26, 14, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast", -1},          // a rank buffer off 16 bytes
+      {127, int64_t(1) << 26, 14, AR_GROUP_CYCLIC, 3, 5, 0, "broadcast", -1},          // gaps, grid above 2^32 work-items
+      {127, int64_t(1) << 26, 14, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 1},    // a rank buffer off 16 bytes
+      {127, int64_t(1) << 22, 14, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 0},    // the same at 16 MiB
+      {127, (int64_t(1) << 22) + 1, 14, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 1},
       {127, int64_t(1) << 25, 14, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 1},   // 128 MiB per rank: XCD regions
       {127, int64_t(1) << 24, 14, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 1},   // 64 MiB
       {127, (int64_t(1) << 24) - 1024, 14, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 1},
@@ -533,7 +548,8 @@ static void broadcast_choice() {
       {64, int64_t(1) << 23, 12, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 1},       // 32 MiB: regions
       {32, int64_t(1) << 24, 10, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 1},       // gradient-sync shape, 64 MiB
       {127, 2304, 14, AR_GROUP_CYCLIC, 8, 0, 0, "broadcast_stream", 0},                // flat columns, root rank 0
-      {127, 2304, 14, AR_GROUP_CYCLIC, 8, 3, 0, "broadcast", -1},
+      {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 8, 0, "broadcast_stream", 1},             // gaps on sectors, 72 MiB per rank
+      {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 3, 0, "broadcast_stream", 0},             // off them: interleaved
       {128, 2304, 14, AR_GROUP_XOR, 4, 0, 0, "broadcast_stream", 0},
       {48, 2304, 12, AR_GROUP_CYCLIC, 8, 0, 0, "broadcast_stream", 0},                  // flat, any P
       {48, 2304, 12, AR_GROUP_CYCLIC, 8192, 0, 0, "broadcast_stream", 1},               // flat, 72 MiB per rank: regions
@@ -545,7 +561,8 @@ static void broadcast_choice() {
 
 static void check_broadcast_case(const BcastCase& c) {
   ar_plan* pl = nullptr;
-  EXPECT(ar_plan_create_ex(c.P, c.n, AR_FLOAT32, AR_SUM, c.k, ar_group(c.group), AR_SCHEDULE_BUTTERFLY, &pl) ==
+  EXPECT(ar_plan_create_ex(c.P, c.n, AR_FLOAT32, AR_SUM, c.k, c.group < 0 ? AR_GROUP_CYCLIC : ar_group(c.group),
+                           c.group < 0 ? AR_SCHEDULE_RING : AR_SCHEDULE_BUTTERFLY, &pl) ==
              AR_OK, "broadcast choice: create P=%d n=%lld", c.P, (long long)c.n);
   if (!pl) return;
   ar_stats s;
@@ -564,13 +581,11 @@ static void check_broadcast_case(const BcastCase& c) {
   ar_plan_destroy(pl);
 }
 
-// Block tiles (AR_FUSED_ROTATE=0) whose blocks all start on the chunk grid:
-// XCD regions from 104 ranks or from 32 MiB per rank, interleaved chunks
-// below.  Plans read the variable when they are created: single-threaded
-// only.
+// Block tiles (AR_FUSED_ROTATE=0): the order of flat columns.  Plans read the
+// variable when they are created: single-threaded only.
 static void broadcast_block_order() {
   const BcastCase cases[] = {
-      {128, int64_t(1) << 21, 14, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 1},      // P >= 104: regions
+      {128, int64_t(1) << 21, 14, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 0},      // 8 MiB: interleaved
       {64, int64_t(1) << 22, 12, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 0},       // 16 MiB: interleaved
       {64, int64_t(1) << 23, 12, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 1},       // 32 MiB: regions
       {32, int64_t(1) << 24, 10, AR_GROUP_XOR, 1, 0, 0, "broadcast_stream", 1},       // 64 MiB
@@ -597,7 +612,7 @@ static void broadcast_order_override() {
   };
   const Case cases[] = {
       {127, int64_t(1) << 26, 1, "2", "broadcast_stream", 0}, {127, int64_t(1) << 26, 1, "3", "broadcast_stream", 1},
-      {127, int64_t(1) << 26, 1, "1", "broadcast_stream", 0}, {127, 127 * 1024 + 77, 1, "1", "broadcast_stream", 0},
+      {127, int64_t(1) << 26, 1, "1", "broadcast_stream", 1}, {127, 127 * 1024 + 77, 1, "1", "broadcast_stream", 0},
       {127, 127 * 1024 + 77, 1, "2", "broadcast_stream", 0},  {127, 127 * 1024 + 77, 1, "3", "broadcast_stream", 1},
       {127, 127 * 1024 + 77, 1, "0", "broadcast", -1},         {127, 2304, 8, "1", "broadcast_stream", 0},
       {127, 2304, 8, "3", "broadcast_stream", 1},              {48, 2304, 8, "2", "broadcast_stream", 0},
