@@ -204,8 +204,11 @@ typedef struct {
                                         destination -- flat columns, or rank buffers of
                                         at least 2 MiB (AR_BCAST_STREAM overrides the
                                         size rule), for rank buffers of any alignment
-                                        and instances with or without gaps whose span,
-                                        (batch - 1) * instance_stride + n, is below
+                                        and instances without gaps, or with gaps no
+                                        wider than an instance (a multiple of 16
+                                        elements: 3/8 of one, 1/8 or 1/16 for instances
+                                        below 512 elements; any with the override), whose
+                                        span, (batch - 1) * instance_stride + n, is below
                                         2^32 - 2048 elements; other calls, and 0 here,
                                         take the tiled broadcast (the same bits)          */
 } ar_stats;

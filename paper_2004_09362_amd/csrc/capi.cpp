@@ -384,6 +384,24 @@ uint32_t xcd_count(int device) {
   return uint32_t(std::max<int32_t>(1, c / 32));
 }
 
+// Whether gaps between instances are narrow enough for the destination-major
+// copy, whose workgroups walk a rank's whole span, gaps included, where the
+// tiled copy visits columns only.  The tiled copy streams whole lines where the
+// gap is a multiple of 32 elements, half lines at 16, and parts of lines
+// elsewhere.  Time of this copy's call over the tiled one's, P = 33-127, 4 and
+// 16 MiB per rank:
+//   other gaps, stride / n 1.25 0.63-1.0, 1.5 0.66-1.04, 2 0.72-1.0, 3 0.85-1.18;
+//   multiples of 16, n = 128 stride 160 0.94-1.09, 192 1.02-1.16, 256 1.2-1.4; n =
+//   256 stride 272 0.78-1.1, 288 0.88-1.0; n = 2304 stride 2880 0.88-0.93, 3456
+//   0.96-1.02, 4608 1.14-1.19; n = 16384 stride 2 n 1.23-1.27;
+//   any gap, stride 16 n 3-6, 64 n 15-24.
+bool narrow_gaps(int64_t n, int64_t stride) {
+  const int64_t gap = stride - n;
+  if (gap % 16 != 0) return gap <= n;
+  if (n < 512) return gap <= (gap % 32 == 0 ? n / 8 : n / 16);
+  return gap <= n / 8 * 3;
+}
+
 struct CopyCall {
   ar::CopyArgs a;
   uint32_t grid;
@@ -391,7 +409,7 @@ struct CopyCall {
 };
 
 // The destination-major copy (broadcast.hip) of a split call, where the size
-// rule or an override asks for it and its 32-bit positions hold a rank's span;
+// rules or an override ask for it and its 32-bit positions hold a rank's span;
 // false: the tiled copy runs.
 //
 // With gaps between the instances, ones that start off 32-byte sectors (a
@@ -409,6 +427,7 @@ bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stri
   if (mode == 0 || (mode < 0 && !flat && span * 4 < kBcastStreamMinBytes)) return false;
   if (span > int64_t(UINT32_MAX) - 2 * int64_t(ar::kStreamChunk)) return false;
   const bool gap = batch > 1 && stride != n;
+  if (gap && mode < 0 && !narrow_gaps(n, stride)) return false;
   const bool sectors = !gap || (stride % 8 == 0 && n >= 512);
   const uint32_t xcds = xcd_count(device);
   uint32_t shift = 0;

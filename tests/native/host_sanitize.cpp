@@ -550,6 +550,17 @@ static void broadcast_choice() {
       {127, 2304, 14, AR_GROUP_CYCLIC, 8, 0, 0, "broadcast_stream", 0},                // flat columns, root rank 0
       {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 8, 0, "broadcast_stream", 1},             // gaps on sectors, 72 MiB per rank
       {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 3, 0, "broadcast_stream", 0},             // off them: interleaved
+      // gaps on both sides of the width that the copy walks: other widths, multiples of 32 and of 16
+      {64, 106, 12, AR_GROUP_CYCLIC, 8000, 106, 0, "broadcast_stream", 0},
+      {64, 106, 12, AR_GROUP_CYCLIC, 8000, 107, 0, "broadcast", -1},
+      {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 864, 0, "broadcast_stream", 1},
+      {127, 2304, 14, AR_GROUP_CYCLIC, 4096, 896, 0, "broadcast", -1},
+      {127, 2304, 14, AR_GROUP_CYCLIC, 512, 34560, 0, "broadcast", -1},
+      {127, 256, 14, AR_GROUP_CYCLIC, 2000, 32, 0, "broadcast_stream", 0},
+      {127, 256, 14, AR_GROUP_CYCLIC, 2000, 64, 0, "broadcast", -1},
+      {127, 256, 14, AR_GROUP_CYCLIC, 2000, 16, 0, "broadcast_stream", 0},
+      {127, 256, 14, AR_GROUP_CYCLIC, 2000, 48, 0, "broadcast", -1},
+      {24, int64_t(1) << 24, 10, AR_GROUP_CYCLIC, 2, int64_t(1) << 24, 0, "broadcast", -1},  // block tiles
       {128, 2304, 14, AR_GROUP_XOR, 4, 0, 0, "broadcast_stream", 0},
       {48, 2304, 12, AR_GROUP_CYCLIC, 8, 0, 0, "broadcast_stream", 0},                  // flat, any P
       {48, 2304, 12, AR_GROUP_CYCLIC, 8192, 0, 0, "broadcast_stream", 1},               // flat, 72 MiB per rank: regions
