@@ -203,14 +203,15 @@ typedef struct {
                                         broadcast of one instance copies destination by
                                         destination -- flat columns, or rank buffers of
                                         at least 2 MiB (AR_BCAST_STREAM overrides the
-                                        size rule), for rank buffers of any alignment
-                                        and instances without gaps, or with gaps no
+                                        size rule), for rank buffers on 128-byte lines
+                                        without gaps between instances and, from 128 MiB
+                                        over all ranks, at any alignment and with gaps no
                                         wider than an instance (a multiple of 16
                                         elements: 3/8 of one, 1/8 or 1/16 for instances
-                                        below 512 elements; any with the override), whose
-                                        span, (batch - 1) * instance_stride + n, is below
-                                        2^32 - 2048 elements; other calls, and 0 here,
-                                        take the tiled broadcast (the same bits)          */
+                                        below 512 elements) -- any call with the override
+                                        -- whose span, (batch - 1) * instance_stride + n,
+                                        is below 2^32 - 2048 elements; other calls, and 0
+                                        here, take the tiled broadcast (the same bits)    */
 } ar_stats;
 
 /* One launch of the STEPWISE path: a list of placement ranges.  In a range,

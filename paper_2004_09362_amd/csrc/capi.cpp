@@ -438,14 +438,20 @@ bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stri
   // cached stores were up to 6% faster on some shapes (P = 64 at 16 MB per
   // rank, flat columns), but the pair then took 0.3-10% longer: the next
   // reducing launch pays for the cached lines (P = 32-128, 4-256 MB per rank)
-  const bool want_nt = pl->bcast_nt_mode == 1 ||
-                       (pl->bcast_nt_mode < 0 && int64_t(P) * n * batch * 4 >= kFusedNtThresholdBytes);
+  const bool big = int64_t(P) * n * batch * 4 >= kFusedNtThresholdBytes;
+  const bool want_nt = pl->bcast_nt_mode == 1 || (pl->bcast_nt_mode < 0 && big);
   std::memset(c, 0, sizeof *c);
   for (int32_t x = 0; x < P; ++x) {
     c->a.user[x] = bufs[x];
     if (x > 0 && reinterpret_cast<uintptr_t>(bufs[x]) % 128 != 0) c->lines = true;
   }
   c->lines = c->lines || gap;
+  // Rows off the lines, and gaps, in calls that the caches hold: the tiled copy,
+  // which reads a column once for its P - 1 stores.  Whole calls, this copy over
+  // the tiled one: P = 33-127 at 0.5 MiB per rank 1.1-1.8, at 1 MiB 1.0-1.5 up to
+  // 64 ranks and 0.9-1.05 from 100, at 2 MiB 1.0-1.1 up to 40 ranks; from
+  // kFusedNtThresholdBytes on 0.56-0.93.
+  if (mode < 0 && c->lines && !big) return false;
   // The slices of a call are evened out and rounded up to the XCD count: a
   // short last slice in regions leaves most XCDs idle.
   const uint64_t per_xcd = !regions ? kCopyInterleavedChunks

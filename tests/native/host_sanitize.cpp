@@ -550,6 +550,13 @@ static void broadcast_choice() {
       {127, 2304, 14, AR_GROUP_CYCLIC, 8, 0, 0, "broadcast_stream", 0},                // flat columns, root rank 0
       {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 8, 0, "broadcast_stream", 1},             // gaps on sectors, 72 MiB per rank
       {127, 2304, 14, AR_GROUP_CYCLIC, 8192, 3, 0, "broadcast_stream", 0},             // off them: interleaved
+      // off the lines, or with gaps: by the tiles in calls below 128 MiB over all ranks
+      {64, 524287, 12, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast", -1},
+      {64, 524288, 12, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 0},
+      {64, 524287, 12, AR_GROUP_CYCLIC, 1, 0, 0, "broadcast_stream", 0},
+      {40, 1000, 12, AR_GROUP_CYCLIC, 800, 3, 0, "broadcast", -1},
+      {40, 1000, 12, AR_GROUP_CYCLIC, 840, 3, 0, "broadcast_stream", 0},
+      {40, 1000, 12, AR_GROUP_CYCLIC, 800, 0, 64, "broadcast", -1},
       // gaps on both sides of the width that the copy walks: other widths, multiples of 32 and of 16
       {64, 106, 12, AR_GROUP_CYCLIC, 8000, 106, 0, "broadcast_stream", 0},
       {64, 106, 12, AR_GROUP_CYCLIC, 8000, 107, 0, "broadcast", -1},
