@@ -208,7 +208,8 @@ typedef struct {
                                         over all ranks, at any alignment and with gaps no
                                         wider than an instance (a multiple of 16
                                         elements: 3/8 of one, 1/8 or 1/16 for instances
-                                        below 512 elements) -- any call with the override
+                                        below 512 elements; of 32 with a stride that is
+                                        no multiple of 8: none) -- any with the override
                                         -- whose span, (batch - 1) * instance_stride + n,
                                         is below 2^32 - 2048 elements; other calls, and 0
                                         here, take the tiled broadcast (the same bits)    */

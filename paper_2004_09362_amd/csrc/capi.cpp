@@ -394,10 +394,13 @@ uint32_t xcd_count(int device) {
 //   multiples of 16, n = 128 stride 160 0.94-1.09, 192 1.02-1.16, 256 1.2-1.4; n =
 //   256 stride 272 0.78-1.1, 288 0.88-1.0; n = 2304 stride 2880 0.88-0.93, 3456
 //   0.96-1.02, 4608 1.14-1.19; n = 16384 stride 2 n 1.23-1.27;
+//   multiples of 32 under strides off the 32-byte sectors (cached stores), n = 1999
+//   stride 2031 0.87-1.1, 2991 1.0-1.2;
 //   any gap, stride 16 n 3-6, 64 n 15-24.
 bool narrow_gaps(int64_t n, int64_t stride) {
   const int64_t gap = stride - n;
   if (gap % 16 != 0) return gap <= n;
+  if (gap % 32 == 0 && stride % 8 != 0) return false;
   if (n < 512) return gap <= (gap % 32 == 0 ? n / 8 : n / 16);
   return gap <= n / 8 * 3;
 }

@@ -567,6 +567,9 @@ static void broadcast_choice() {
       {127, 256, 14, AR_GROUP_CYCLIC, 2000, 64, 0, "broadcast", -1},
       {127, 256, 14, AR_GROUP_CYCLIC, 2000, 16, 0, "broadcast_stream", 0},
       {127, 256, 14, AR_GROUP_CYCLIC, 2000, 48, 0, "broadcast", -1},
+      {100, 4111, 14, AR_GROUP_CYCLIC, 1020, 64, 0, "broadcast", -1},
+      {100, 4111, 14, AR_GROUP_CYCLIC, 1020, 65, 0, "broadcast_stream", 1},
+      {100, 4112, 14, AR_GROUP_CYCLIC, 1020, 64, 0, "broadcast_stream", 1},
       {24, int64_t(1) << 24, 10, AR_GROUP_CYCLIC, 2, int64_t(1) << 24, 0, "broadcast", -1},  // block tiles
       {128, 2304, 14, AR_GROUP_XOR, 4, 0, 0, "broadcast_stream", 0},
       {48, 2304, 12, AR_GROUP_CYCLIC, 8, 0, 0, "broadcast_stream", 0},                  // flat, any P
