@@ -103,7 +103,8 @@ typedef enum { AR_SUM = 0, AR_MAX = 1 } ar_op;
  *                                   same result (default: split for
  *                                   P >= 64, for P >= 24 when n * e is at
  *                                   least 32 MiB, and for P >= 33 in the
- *                                   rank-slot kernel);
+ *                                   rank-slot kernel; int32 calls: see
+ *                                   fused_launches);
  *   AR_BCAST_NT = 0|1               nontemporal loads and stores in that
  *                                   broadcast (default, for launches of 128
  *                                   MiB and more: the tiled copy with
@@ -181,8 +182,13 @@ typedef struct {
                                         at least 32 MiB; P >= 33 in the rank-slot
                                         kernel).  int32 plans, whose combinations give
                                         the same bits in any order, have one result at
-                                        every k and split for P >= 17 when n * e is at
-                                        least 4 MiB or P * n * e at least 192 MiB        */
+                                        every k and split call by call for P >= 17: where
+                                        P * n * batch * e is at least 128 MiB (200 MiB
+                                        for P < 33) on 128-byte lines without gaps,
+                                        288 MiB otherwise (instances of 512 elements or
+                                        more off the lines; behind wide gaps from
+                                        P = 48).  This and hbm_bytes_fused
+                                        state one instance on the lines                  */
   int32_t fused_flat;                /* FUSED path with short blocks (sums; max in the
                                         bandwidth-optimal, Ring and XOR plans), and on
                                         long blocks the AR_FUSED_ROTATE defaults: 1

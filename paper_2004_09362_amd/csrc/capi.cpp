@@ -39,14 +39,25 @@ constexpr int64_t kFusedNtThresholdBytes = int64_t(128) << 20;
 constexpr int32_t kSplitMinP = 64;
 constexpr int32_t kSplitMidMinP = 24;
 constexpr int64_t kSplitMidMinBytes = int64_t(32) << 20;
-// int32 plans (any k, group and schedule: one result) split from
-// kFreeSplitMinP ranks where an instance holds kFreeSplitMinBytes per rank or
-// kFreeSplitMinTotal over all ranks.  On one launch / split, TB/s: P = 24 at
-// 4 MB per rank 5.0 / 4.7, at 16 MB 5.6 / 6.1, at 128 MB 6.1 / 6.45; P = 64 at
-// 2 MB 5.5 / 5.3, at 16 MB 5.8 / 6.9; P = 127 at 1 MB 5.5 / 4.6, at 2 MB 5.25 /
-// 5.85; P = 16 at 128 MB 6.4 / 6.1, off the 128-byte lines 5.6 / 6.0.
-constexpr int32_t kFreeSplitMinP = 17;
-constexpr int64_t kFreeSplitMinBytes = int64_t(4) << 20, kFreeSplitMinTotal = int64_t(192) << 20;
+// int32 calls (any k, group and schedule: one result) split from
+// kFreeSplitMinP ranks by the bytes of the call over all ranks, all instances
+// together.  On the 128-byte lines from kFreeSplitBytes, below kFreeSplitManyP
+// ranks from kFreeSplitFewBytes: one launch / split took at 128 MiB 1.0-1.18 (rows a
+// power of two apart 0.93-1.05), at 192 MiB and P = 17-28 1.03-1.14 (0.86-0.89), at
+// 256 MiB and more 1.0-1.35 (1.0-1.13); at 96 MiB 0.92-1.05, at 64 0.73-0.98.  From
+// kFreeSplitOddBytes off the lines or with
+// gaps between the instances (256 MiB 0.81-0.88, 320 1.05-1.22; batches of 2304 at
+// stride 2311, 254 MB 0.82-0.87, 384-512 MB 1.02-1.11).  Instances below
+// kFreeSplitMinGapped elements that start off the lines stay on one launch (106 at
+// stride 113: 0.87-1.09).  Behind gaps too wide for the destination-major copy the
+// tiled one pays from kFreeSplitTiledMinP ranks where its waves lie on half lines
+// (gaps of a multiple of 16; 48 at stride 80, P = 64 1.3) or instances are long (2304,
+// P = 37 0.95-1.0, P = 64 1.04, P = 127 1.1; 1000, P = 64 0.83).
+constexpr int32_t kFreeSplitMinP = 17, kFreeSplitTiledMinP = 48;
+constexpr int32_t kFreeSplitManyP = 33;
+constexpr int64_t kFreeSplitBytes = int64_t(128) << 20, kFreeSplitFewBytes = int64_t(200) << 20;
+constexpr int64_t kFreeSplitOddBytes = int64_t(288) << 20;
+constexpr int64_t kFreeSplitMinGapped = 512, kFreeSplitTiledMinLen = 2048;
 // Flat short-block sums in the rank-slot kernel (not the XOR group's) split
 // from this many ranks up: their single launch streams 5.0-5.6 TB/s there and
 // the pair up to 6.0 (P = 37: 7%, P = 48: 15% faster with caps 4 and 2 and a
@@ -193,7 +204,8 @@ struct ar_plan {
   // allow; default: for blocks of up to kMergeMaxLen elements).
   int32_t nt_mode = -1, fused_nt_mode = -1, split_mode = -1, bcast_nt_mode = -1, bcast_stream_mode = -1;
   int32_t packed_mode = -1, rotate_mode = -1, merge_mode = -1;
-  bool fused_split = false;
+  bool fused_split = false;  // int32 plans: one instance on the lines (call_splits decides for a call)
+  bool any_order = false;    // int32: combinations give the same bits in any order
   // Sums whose blocks hold at most kPackMaxLen elements run on flat columns
   // whenever the batch's columns fit in 32 bits: the cyclic butterfly plans
   // with r < L and the Ring in the rank-slot kernel, the XOR group's plans
@@ -403,6 +415,26 @@ bool narrow_gaps(int64_t n, int64_t stride) {
   if (gap % 32 == 0 && stride % 8 != 0) return false;
   if (n < 512) return gap <= (gap % 32 == 0 ? n / 8 : n / 16);
   return gap <= n / 8 * 3;
+}
+
+// Whether int32 calls of this many bytes over all ranks split by default.
+bool free_splits(int32_t P, int64_t n, int64_t batch, bool on_lines, bool gaps) {
+  const int64_t least = !on_lines || gaps ? kFreeSplitOddBytes : P < kFreeSplitManyP ? kFreeSplitFewBytes : kFreeSplitBytes;
+  return P >= kFreeSplitMinP && n * batch >= least / 4 / P;
+}
+
+// Whether a call runs as a reducing launch and a copy.
+bool call_splits(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stride) {
+  if (!pl->any_order || pl->split_mode >= 0) return pl->fused_split;
+  const int64_t n = pl->s.n;
+  const bool gaps = batch > 1 && stride != n;
+  const bool on_lines = ar::rows_on_lines(bufs, pl->s.P) && (!gaps || stride % 32 == 0);
+  if (gaps && narrow_gaps(n, stride)) {
+    if (n < kFreeSplitMinGapped && !on_lines) return false;
+  } else if (gaps) {
+    if (pl->s.P < kFreeSplitTiledMinP || (n < kFreeSplitTiledMinLen && (stride - n) % 16 != 0)) return false;
+  }
+  return free_splits(pl->s.P, n, batch, on_lines, gaps);
 }
 
 struct CopyCall {
@@ -664,7 +696,8 @@ ar_status run_fused_col(ar_plan* pl, void* const* bufs, int64_t batch, int64_t s
   for (int32_t x = 0; x < 2 * s.P; ++x) a.user[x] = bufs[x % s.P];
   a.P = s.P;
   a.r = s.r;
-  a.split = pl->fused_split ? 1 : 0;
+  const bool split = call_splits(pl, bufs, batch, stride);
+  a.split = split ? 1 : 0;
   a.stride = stride;
   a.n = s.n;
   a.instances = batch;
@@ -720,7 +753,7 @@ ar_status run_fused_col(ar_plan* pl, void* const* bufs, int64_t batch, int64_t s
   else e = ar::launch_fused_col_any(a, s.P, pl->dtype, pl->op, nt, grid, stream);
   if (e != 0) return hip_fail(hipError_t(e), "column-fused kernel launch");
   if (tm) tm->mark();
-  if (pl->fused_split) {
+  if (split) {
     CopyCall c;
     if (copy_call(pl, bufs, batch, stride, a.flat != 0, device, &c)) {
       e = ar::launch_copy(c.a, c.grid, c.nt, c.gap, c.lines, stream);
@@ -762,7 +795,7 @@ ar_status execute_impl(ar_plan* plan, void* const* rank_buffers, int64_t batch, 
     return fail(AR_ERR_NO_DEVICE, std::string("no usable GPU: ") + hipGetErrorString(he));
   }
   const bool fused = plan->path == AR_PATH_FUSED || (plan->path == AR_PATH_AUTO && plan->fused_ok);
-  if (fused && (plan->fused_kind != kFusedLo || plan->fused_split)) {
+  if (fused && (plan->fused_kind != kFusedLo || call_splits(plan, rank_buffers, batch, instance_stride))) {
     st = run_fused_col(plan, rank_buffers, batch, instance_stride, stream, device, tm);
   } else if (fused) {
     st = run_fused_lo(plan, rank_buffers, batch, instance_stride, stream, device, tm);
@@ -849,8 +882,9 @@ double model_seconds(const ar_plan* pl, const ar_model_params& mp, int64_t batch
   const ar::Schedule& s = pl->s;
   if (s.P < 2 || s.n == 0) return 0.0;
   if (path == AR_PATH_FUSED) {
-    const double launches = pl->fused_split ? 2.0 : 1.0;
-    const double bytes = double(int64_t(2) * s.P + (pl->fused_split ? 1 : 0)) * double(s.n) * 4.0 * double(batch);
+    const bool split = pl->any_order && pl->split_mode < 0 ? free_splits(s.P, s.n, batch, true, false) : pl->fused_split;
+    const double launches = split ? 2.0 : 1.0;
+    const double bytes = double(int64_t(2) * s.P + (split ? 1 : 0)) * double(s.n) * 4.0 * double(batch);
     return launches * mp.fused_alpha + bytes / mp.fused_bytes_per_s;
   }
   const double bytes = double(s.hbm_blocks) * double(s.n) * 4.0 * double(batch);
@@ -903,9 +937,8 @@ ar_status create_plan(int32_t P, int64_t n, ar_dtype dtype, ar_op op, int32_t k_
   pl->fused_ok = pl->fused_kind != kFusedNone;
   // one result for every rank: the Ring, r = 0 outside the flat LO kernel, and
   // every int32 plan, whose combinations give the same bits in any order
-  const bool any_order = pl->s.P >= 2 && pl->dtype == AR_INT32;
-  const bool one_result = any_order ||
-pl->fused_kind == kFusedRing ||
+  pl->any_order = pl->s.P >= 2 && pl->dtype == AR_INT32;
+  const bool one_result = pl->any_order || pl->fused_kind == kFusedRing ||
                           ((pl->fused_kind == kFusedCol || pl->fused_kind == kFusedXor) && pl->s.r == 0);
   {
     const int64_t max_len = pl->s.P > 0 ? pl->s.n / pl->s.P + (pl->s.n % pl->s.P ? 1 : 0) : 0;
@@ -935,9 +968,8 @@ pl->fused_kind == kFusedRing ||
   const bool rank_slots = pl->fused_flat && pl->fused_kind != kFusedXor;
   const int32_t split_min =
       rank_slots ? kFlatSplitMinP : (pl->s.n * 4 >= kSplitMidMinBytes ? kSplitMidMinP : kSplitMinP);
-  const bool split_by_size = any_order ? pl->s.P >= kFreeSplitMinP && (pl->s.n * 4 >= kFreeSplitMinBytes ||
-                                                                       pl->s.n * 4 >= kFreeSplitMinTotal / pl->s.P)
-                                       : pl->s.P >= split_min;
+  const bool split_by_size =
+      pl->any_order ? free_splits(pl->s.P, pl->s.n, 1, true, false) : pl->s.P >= split_min;
   pl->fused_split = one_result && (pl->split_mode == 1 || (pl->split_mode < 0 && split_by_size));
   {
     const int32_t P = pl->s.P;

@@ -602,6 +602,58 @@ static void check_broadcast_case(const BcastCase& c) {
   ar_plan_destroy(pl);
 }
 
+// int32 calls split by their own bytes: every k and schedule alike, batches by
+// all their instances, on both sides of the sizes for rows on the 128-byte lines
+// and off them, and with gaps.
+static void int32_split_choice() {
+  struct Case {
+    int P;
+    int64_t n, batch, gap;
+    uintptr_t misalign;
+    size_t launches;
+  };
+  const Case cases[] = {
+      {16, int64_t(1) << 24, 1, 0, 0, 1},    // below 17 ranks
+      {17, int64_t(1) << 20, 1, 0, 0, 1},    // 68 MiB
+      {64, (int64_t(1) << 19) - 32, 1, 0, 0, 1}, {64, int64_t(1) << 19, 1, 0, 0, 2},  // 128 MiB
+      {24, int64_t(1) << 21, 1, 0, 0, 1}, {24, 100 << 14, 1, 0, 0, 1},
+      {32, 100 << 14, 1, 0, 0, 2}, {25, int64_t(1) << 21, 1, 0, 0, 2},  // 200 MiB below 33 ranks
+      {24, (3 << 19) - 32, 2, 0, 4, 1}, {24, 3 << 20, 1, 0, 4, 2},  // off the lines 288 MiB
+      {37, 106, 65536, 0, 0, 2}, {64, 106, 65536, 0, 0, 2}, {127, 106, 65536, 0, 0, 2},
+      {127, 106, 2400, 0, 0, 1}, {127, 106, 2550, 0, 0, 2},
+      {127, 2304, 8192, 0, 0, 2},
+      {64, 2304, 400, 7, 0, 1}, {64, 2304, 600, 7, 0, 2},  // gaps, 225 and 338 MiB
+      {64, 106, 65536, 7, 0, 1}, {64, 106, 65536, 54, 0, 2},  // short instances off the lines and on them
+      {64, 2000, 600, 2000 * 9 + 1, 0, 1}, {64, 2304, 600, 2304 * 9 + 1, 0, 2}, {37, 2304, 1200, 2304 * 9, 0, 1},  // tiled
+      {64, 48, 87381, 32, 0, 2}, {37, 48, 87381, 32, 0, 1},
+  };
+  for (const Case& c : cases) {
+    const int L = ceil_log2(c.P);
+    const int64_t stride = c.n + c.gap;
+    for (int kind = 0; kind < 3; ++kind) {
+      ar_plan* pl = nullptr;
+      const ar_status st = ar_plan_create_ex(c.P, c.n, AR_INT32, kind == 1 ? AR_MAX : AR_SUM,
+                                             kind == 0 ? L : kind == 1 ? 2 * L : 2 * (c.P - 1), AR_GROUP_CYCLIC,
+                                             kind == 2 ? AR_SCHEDULE_RING : AR_SCHEDULE_BUTTERFLY, &pl);
+      EXPECT(st == AR_OK && pl, "int32 split: create P=%d n=%lld", c.P, (long long)c.n);
+      if (!pl) return;
+      ar_stats s;
+      EXPECT(ar_plan_stats(pl, &s) == AR_OK && (c.batch > 1 || c.misalign || size_t(s.fused_launches) == c.launches),
+             "int32 split: stats P=%d n=%lld say %d launches", c.P, (long long)c.n, s.fused_launches);
+      std::vector<void*> bufs = fake_buffers(c.P, ((c.batch - 1) * stride + c.n) * 4 + 64);
+      bufs[1] = reinterpret_cast<char*>(bufs[1]) + c.misalign;
+      fake::launches.clear();
+      EXPECT(ar_execute_batched(pl, bufs.data(), c.batch, stride, stream_tag()) == AR_OK &&
+                 fake::launches.size() == c.launches &&
+                 (c.launches == 1 || std::strncmp(fake::launches[1].kind, "broadcast", 9) == 0),
+             "int32 split: P=%d n=%lld batch %lld gap %lld misalign %zu kind %d made %zu launches, expected %zu", c.P,
+             (long long)c.n, (long long)c.batch, (long long)c.gap, size_t(c.misalign), kind, fake::launches.size(),
+             c.launches);
+      ar_plan_destroy(pl);
+    }
+  }
+}
+
 // Block tiles (AR_FUSED_ROTATE=0): the order of flat columns.  Plans read the
 // variable when they are created: single-threaded only.
 static void broadcast_block_order() {
@@ -887,6 +939,7 @@ int main(int argc, char** argv) {
       errors();
       execute_errors();
       broadcast_choice();
+      int32_split_choice();
     });
     for (int t = 0; t < nt; ++t) th.emplace_back([t, nt, pmax, &counts] { counts[size_t(t)] = sweep(1 + t, nt, pmax); });
     for (std::thread& x : th) x.join();
@@ -896,6 +949,7 @@ int main(int argc, char** argv) {
     errors();
     execute_errors();
     broadcast_choice();
+    int32_split_choice();
     broadcast_order_override();
     broadcast_block_order();
     plans = sweep(1, 1, pmax);
