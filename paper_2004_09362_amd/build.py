@@ -20,7 +20,7 @@ SOURCES = [os.path.join(CSRC, f) for f in ["plan.cpp", "capi.cpp", "kernels.hip"
                                            "fused_free.hip", "fused_small.hip",
                                            "broadcast.hip", "noalloc.hip"]]
 HEADERS = [os.path.join(CSRC, f) for f in ("ar_internal.hpp", "device_common.hpp", "fused_col.hpp",
-                                               "fused_free.hpp")] + [
+                                               "fused_free.hpp", "free_shape.hpp")] + [
     os.path.join(ROOT, "include", "ar.h")]
 # The native part of the Python binding: host code only, against torch's and Python's headers.
 BIND_SOURCE = os.path.join(CSRC, "bind.cpp")
@@ -163,7 +163,7 @@ FAMILIES = {
     "lo": ["fused_lo.hip"],
     "col": ["fused_col.hpp"],  # and the generated units (col_unit_text)
     "group": ["fused_group.hip"],
-    "free": ["fused_free.hip", "fused_free.hpp"],
+    "free": ["fused_free.hip", "fused_free.hpp", "free_shape.hpp"],
     "small": ["fused_small.hip"],
     "bcast": ["broadcast.hip"],
 }

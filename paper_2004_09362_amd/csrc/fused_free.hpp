@@ -16,8 +16,8 @@
 // Instantiated for every P = 2..128 in the units that build.py writes.
 //
 // Bound by HBM (P reads and P writes, or one, of every column; one operation
-// per element); the widths, caps and store kinds are chosen in fused_free.hip
-// (free_shape), with what they measured.
+// per element); the widths, caps and store kinds are chosen in
+// free_shape.hpp, with what they measured.
 #pragma once
 
 #include "device_common.hpp"

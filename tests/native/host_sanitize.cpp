@@ -42,6 +42,7 @@
 
 #include "ar.h"
 #include "ar_internal.hpp"
+#include "free_shape.hpp"
 
 // ---------------------------------------------------------------------------
 // Fake HIP runtime: one device, allocations that return distinct fake
@@ -654,6 +655,33 @@ static void int32_split_choice() {
   }
 }
 
+// int32 launches with gaps: cached up to 640 MiB of traffic, and above it where an
+// instance is short and less than a line follows it; a launch without gaps streams
+// on the lines from the size that `big` states.
+static void int32_gap_accesses() {
+  struct Case {
+    int P;
+    int64_t mib, n, gap;
+    bool lines, nt;
+  };
+  const Case cases[] = {
+      {4, 200, 1000, 24, true, false}, {16, 500, 1000, 24, true, false}, {16, 640, 1000, 24, true, true},
+      {2, 639, 2304, 64, true, false}, {3, 800, 1000, 1, false, true},   {3, 200, 1000, 1, false, false},
+      {8, 800, 1000, 1, false, false}, {16, 800, 88, 8, true, false},    {16, 800, 88, 40, true, true},
+      {16, 800, 192, 8, true, true},   {16, 200, 1000, 0, true, true},   {127, 800, 1000, 24, true, false},
+  };
+  for (const Case& c : cases) {
+    ar::FusedTuning t{};
+    t.bytes = c.mib << 20;
+    t.nt = -1;
+    t.big = 1;
+    EXPECT(ar::free_shape(c.P, false, c.lines, t, c.n, c.gap).nt == c.nt, "int32 accesses: P=%d %lld MiB n=%lld gap %lld",
+           c.P, (long long)c.mib, (long long)c.n, (long long)c.gap);
+    t.big = 0;
+    EXPECT(!ar::free_shape(c.P, false, c.lines, t, c.n, c.gap).nt, "int32 accesses: small calls are cached");
+  }
+}
+
 // Block tiles (AR_FUSED_ROTATE=0): the order of flat columns.  Plans read the
 // variable when they are created: single-threaded only.
 static void broadcast_block_order() {
@@ -940,6 +968,7 @@ int main(int argc, char** argv) {
       execute_errors();
       broadcast_choice();
       int32_split_choice();
+      int32_gap_accesses();
     });
     for (int t = 0; t < nt; ++t) th.emplace_back([t, nt, pmax, &counts] { counts[size_t(t)] = sweep(1 + t, nt, pmax); });
     for (std::thread& x : th) x.join();
@@ -950,6 +979,7 @@ int main(int argc, char** argv) {
     execute_errors();
     broadcast_choice();
     int32_split_choice();
+    int32_gap_accesses();
     broadcast_order_override();
     broadcast_block_order();
     plans = sweep(1, 1, pmax);
