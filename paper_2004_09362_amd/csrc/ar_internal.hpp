@@ -224,6 +224,35 @@ struct ColArgs {
   FusedTuning tune;
 };
 
+// Flat columns lie on the 128-byte lines of every rank's buffer: wave rows
+// then cover whole lines.  Block tiles do where the rows are congruent (their
+// tiles are laid on the root's lines).
+inline bool flat_on_lines(const ColArgs& a) {
+  return rows_on_lines(a.user, a.P) &&
+         (a.instances == 1 || a.stride == a.n || (a.stride % 32 == 0 && a.n % 32 == 0));
+}
+
+// Nontemporal accesses of a launch that the host would stream: not off the
+// lines, where each access that covers part of a line costs the whole line
+// (stores twice over), while ordinary ones meet in L2.  Rows back to back at
+// an odd length, one launch, cached / nontemporal, TB/s: P = 8 5.9 / 4.6, P = 13
+// 5.3 / 4.1, P = 24 5.0 / 3.8, P = 64 4.8 / 3.3, P = 127 4.3 / 2.8.  Reducing launches (one
+// store a column) below 48 ranks keep them: P = 24 5.75 / 5.55, P = 64 5.6 / 5.9;
+// so do calls of up to four ranks but those of short instances between gaps:
+// P = 4 5.0 / 5.3, 5184 x 1290 at stride 1322 41.7 / 38.4 us; 106 at 113, P = 3 5.1 / 4.2.
+inline bool stream_nt(const ColArgs& a, bool nt) {
+  if (!nt || a.tune.nt >= 0 || (a.split && a.P < 48)) return nt;
+  if (a.P <= 4 && (a.instances == 1 || a.stride == a.n || a.n >= 1024)) return nt;
+  return a.packed ? false : a.flat ? flat_on_lines(a) : rows_congruent(a.user, a.P);
+}
+
+// The rank-slot kernel's accesses: nontemporal on the lines whatever the size
+// (its launches stream short blocks of many instances once), as in reducing
+// launches below 48 ranks; AR_FUSED_NT overrides both.
+inline bool rot_nt(const ColArgs& a) {
+  return a.tune.nt >= 0 ? a.tune.nt != 0 : (a.split && a.P < 48) || flat_on_lines(a);
+}
+
 // dtype: 0 int32, 1 float32; op: 0 sum, 1 max.  Returns a hipError_t value.
 int launch_step(const StepArgs& a, int dtype, int op, bool vec, bool nt, int grid, void* stream);
 // One step as merged runs (a.run_len, a.tiles, ...): each range's blocks of a

@@ -468,7 +468,7 @@ bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stri
   uint32_t shift = 0;
   while ((1u << shift) < xcds) ++shift;
   const bool want_regions = mode == 2 || mode == 3 ? mode == 3 : span * 4 > kCopyRegionsMinBytes;
-  const bool regions = want_regions && sectors && (1u << shift) == xcds;
+  const bool regions = want_regions && (sectors || mode == 3) && (1u << shift) == xcds;
   // nontemporal at any P for calls of kFusedNtThresholdBytes and more: alone,
   // cached stores were up to 6% faster on some shapes (P = 64 at 16 MB per
   // rank, flat columns), but the pair then took 0.3-10% longer: the next
@@ -506,7 +506,7 @@ bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stri
   }
   c->grid = uint32_t(grid);
   c->gap = gap;
-  c->nt = want_nt && sectors;
+  c->nt = want_nt && (sectors || pl->bcast_nt_mode == 1);
   c->a.P = uint32_t(P);
   c->a.cols = uint32_t(span);
   c->a.n = uint32_t(n);

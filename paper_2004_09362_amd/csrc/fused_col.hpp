@@ -341,8 +341,8 @@ int launch_rot_rr(const ColArgs& a, int grid, hipStream_t s) {
 // whose ranks all receive one result, and at every r for P in
 // [kRotMaxShiftedMinP, kRotMaxShiftedMaxP].  Elsewhere shifted max plans
 // reach this kernel from launch_fused_mid, on short blocks, in its cached
-// form alone.  int32 plans have their own kernel.  Nontemporal on the lines
-// whatever the size: these launches stream short blocks of many instances once.
+// form alone (AR_FUSED_NT = 1 keeps them on packed tiles).  int32 plans have
+// their own kernel.  Accesses: rot_nt (ar_internal.hpp).
 template <int P, bool NT>
 int launch_rot_nt(const ColArgs& a, int op, bool ring, int grid, hipStream_t s) {
   const dim3 g(grid), blk(kBlock);
@@ -370,8 +370,7 @@ int launch_fused_rot(const ColArgs& a, int dtype, int op, bool ring, int grid, v
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);
   if (!ring && small_call(a)) return launch_fused_small(a, op, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  return (a.split && P < 48) || flat_on_lines(a) ? launch_rot_nt<P, true>(a, op, ring, grid, s)
-                                                 : launch_rot_nt<P, false>(a, op, ring, grid, s);
+  return rot_nt(a) ? launch_rot_nt<P, true>(a, op, ring, grid, s) : launch_rot_nt<P, false>(a, op, ring, grid, s);
 }
 
 // fused_wide_kernel: the block-tiled plans of few ranks (P <= 8, r < L) with
@@ -528,7 +527,8 @@ int launch_fused_mid(const ColArgs& a, int dtype, int op, bool nt, int grid, voi
   // 17.2 / 0.70 ms; 39880 x 106, P = 127, 37.8 / 0.98 ms.
   if constexpr (col_L(P) > 1) {
     const int64_t cols = a.n * a.instances;
-    if (op == 1 && a.packed && !a.tune.layout_forced && a.r < col_L(P) && cols < (int64_t(1) << 32) - 64) {
+    if (op == 1 && a.packed && !a.tune.layout_forced && a.tune.nt != 1 && a.r < col_L(P) &&
+        cols < (int64_t(1) << 32) - 64) {
       ColArgs f = a;
       f.packed = 0;
       f.flat = 1;

@@ -682,6 +682,69 @@ static void int32_gap_accesses() {
   }
 }
 
+// AR_BCAST_NT and AR_BCAST_STREAM hold for calls with gaps as for others, also
+// where the rules would take cached stores in interleaved order.  Plans read them
+// when they are created: single-threaded only.
+static void broadcast_overrides_with_gaps() {
+  for (int64_t n : {int64_t(2304), int64_t(106)})
+    for (int nt = -1; nt <= 1; ++nt)
+      for (int order = 1; order <= 3; ++order) {
+        char e[2] = {char('0' + order), 0};
+        setenv("AR_BCAST_STREAM", e, 1);
+        if (nt >= 0) setenv("AR_BCAST_NT", nt ? "1" : "0", 1);
+        ar_plan* pl = nullptr;
+        EXPECT(ar_plan_create(127, n, AR_FLOAT32, AR_SUM, 14, &pl) == AR_OK, "gap overrides: create");
+        unsetenv("AR_BCAST_STREAM");
+        unsetenv("AR_BCAST_NT");
+        if (!pl) return;
+        const int64_t batch = (int64_t(18) << 20) / n;  // 72 MiB per rank
+        std::vector<void*> bufs = fake_buffers(127, batch * (n + 3) * 4);
+        fake::launches.clear();
+        fake::last_regions = fake::last_nt = -1;
+        EXPECT(ar_execute_batched(pl, bufs.data(), batch, n + 3, stream_tag()) == AR_OK && fake::launches.size() == 2 &&
+                   fake::last_nt == (nt == 1 ? 1 : 0) && fake::last_regions == (order == 3 ? 1 : 0),
+               "gap overrides: n=%lld AR_BCAST_NT=%d AR_BCAST_STREAM=%d: nt %d, regions %d", (long long)n, nt, order,
+               fake::last_nt, fake::last_regions);
+        ar_plan_destroy(pl);
+      }
+}
+
+// The accesses of the fp32 launches on flat columns: by the rows' lines, and as
+// AR_FUSED_NT says where it is set.
+static void flat_accesses() {
+  struct Case {
+    int P, split;
+    int64_t n, stride;
+    uintptr_t misalign;
+    bool rot, other;  // nontemporal in the rank-slot kernel, and in the others
+  };
+  const Case cases[] = {
+      {24, 0, 106, 106, 0, true, true},  {24, 0, 106, 106, 4, false, false}, {24, 1, 106, 106, 4, true, true},
+      {64, 1, 106, 106, 4, false, false}, {24, 0, 106, 113, 0, false, false}, {24, 0, 96, 128, 0, true, true},
+      {3, 0, 2000, 2013, 4, false, true}, {3, 0, 106, 113, 4, false, false},
+  };
+  for (const Case& c : cases) {
+    ar::ColArgs a;
+    std::memset(&a, 0, sizeof a);
+    const std::vector<void*> bufs = fake_buffers(c.P, 1 << 20);
+    for (int x = 0; x < c.P; ++x) a.user[x] = bufs[size_t(x)];
+    a.user[1] = reinterpret_cast<char*>(a.user[1]) + c.misalign;
+    a.P = c.P;
+    a.split = c.split;
+    a.flat = 1;
+    a.n = c.n;
+    a.stride = c.stride;
+    a.instances = 9;
+    for (int nt = -1; nt <= 1; ++nt) {
+      a.tune.nt = nt;
+      EXPECT(ar::rot_nt(a) == (nt < 0 ? c.rot : nt == 1), "rank-slot accesses: P=%d n=%lld stride %lld AR_FUSED_NT=%d",
+             c.P, (long long)c.n, (long long)c.stride, nt);
+      EXPECT(ar::stream_nt(a, nt != 0) == (nt < 0 ? c.other : nt == 1), "accesses: P=%d n=%lld stride %lld AR_FUSED_NT=%d",
+             c.P, (long long)c.n, (long long)c.stride, nt);
+    }
+  }
+}
+
 // Block tiles (AR_FUSED_ROTATE=0): the order of flat columns.  Plans read the
 // variable when they are created: single-threaded only.
 static void broadcast_block_order() {
@@ -969,6 +1032,7 @@ int main(int argc, char** argv) {
       broadcast_choice();
       int32_split_choice();
       int32_gap_accesses();
+      flat_accesses();
     });
     for (int t = 0; t < nt; ++t) th.emplace_back([t, nt, pmax, &counts] { counts[size_t(t)] = sweep(1 + t, nt, pmax); });
     for (std::thread& x : th) x.join();
@@ -980,7 +1044,9 @@ int main(int argc, char** argv) {
     broadcast_choice();
     int32_split_choice();
     int32_gap_accesses();
+    flat_accesses();
     broadcast_order_override();
+    broadcast_overrides_with_gaps();
     broadcast_block_order();
     plans = sweep(1, 1, pmax);
   }
