@@ -437,6 +437,8 @@ bool call_splits(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t st
   return free_splits(pl->s.P, n, batch, on_lines, gaps);
 }
 
+constexpr int64_t kCopyFewOddBytes = int64_t(64) << 20;
+
 struct CopyCall {
   ar::CopyArgs a;
   uint32_t grid;
@@ -483,10 +485,13 @@ bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stri
   c->lines = c->lines || gap;
   // Rows off the lines, and gaps, in calls that the caches hold: the tiled copy,
   // which reads a column once for its P - 1 stores.  Whole calls, this copy over
-  // the tiled one: P = 33-127 at 0.5 MiB per rank 1.1-1.8, at 1 MiB 1.0-1.5 up to
-  // 64 ranks and 0.9-1.05 from 100, at 2 MiB 1.0-1.1 up to 40 ranks; from
+  // the tiled one, on one set of buffers / on buffers that alternate beyond the
+  // caches: at 32 MiB over all ranks 1.2-1.8 / 1.05-1.3, at 64 MiB and 48 ranks or more
+  // 1.0-1.4 / 1.05-1.2, at 96-127 MiB 1.0-1.2 / 1.0-1.1; below 48 ranks, whose reducing
+  // launches stream past the caches, 1.04-1.08 / 0.83-0.97 at 64 MiB; from
   // kFusedNtThresholdBytes on 0.56-0.93.
-  if (mode < 0 && c->lines && !big) return false;
+  if (mode < 0 && c->lines && int64_t(P) * n * batch * 4 < (P < 48 ? kCopyFewOddBytes : kFusedNtThresholdBytes))
+    return false;
   // The slices of a call are evened out and rounded up to the XCD count: a
   // short last slice in regions leaves most XCDs idle.
   const uint64_t per_xcd = !regions ? kCopyInterleavedChunks
