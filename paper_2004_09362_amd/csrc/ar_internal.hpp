@@ -224,12 +224,16 @@ struct ColArgs {
   FusedTuning tune;
 };
 
-// Flat columns lie on the 128-byte lines of every rank's buffer: wave rows
-// then cover whole lines.  Block tiles do where the rows are congruent (their
-// tiles are laid on the root's lines).
+// Flat columns lie on the 128-byte lines of every rank's buffer, or on half
+// lines (which HBM serves whole): wave rows then cover whole ones.  So they do
+// where every gap between instances is a multiple of 16 elements, whatever the
+// instances' length.  Block tiles do where the rows are congruent (their tiles are
+// laid on the root's lines).  Rank slots, cached over nontemporal, on buffers that
+// alternate beyond the caches, 120 MB over all ranks, P = 10-100: 48 at stride 64 1.1-1.25, 128
+// at 176 1.22-1.26, 208 at 224 1.1-1.2, 104 at 136 1.02-1.15, 1008 at 1024 0.97-1.1; 104 at 112
+// 0.73-0.86, 106 at 128 0.72-0.93, 500 at 512 0.72-0.87, 1000 at 1024 0.83-0.97.
 inline bool flat_on_lines(const ColArgs& a) {
-  return rows_on_lines(a.user, a.P) &&
-         (a.instances == 1 || a.stride == a.n || (a.stride % 32 == 0 && a.n % 32 == 0));
+  return rows_on_lines(a.user, a.P) && (a.instances == 1 || (a.stride - a.n) % 16 == 0);
 }
 
 // Nontemporal accesses of a launch that the host would stream: not off the

@@ -722,6 +722,8 @@ static void flat_accesses() {
   const Case cases[] = {
       {24, 0, 106, 106, 0, true, true},  {24, 0, 106, 106, 4, false, false}, {24, 1, 106, 106, 4, true, true},
       {64, 1, 106, 106, 4, false, false}, {24, 0, 106, 113, 0, false, false}, {24, 0, 96, 128, 0, true, true},
+      {14, 0, 208, 224, 0, true, true},  {33, 0, 48, 288, 0, true, true},    {24, 0, 104, 136, 0, true, true},
+      {24, 0, 104, 112, 0, false, false}, {24, 0, 500, 512, 0, false, false}, {24, 0, 104, 136, 64, false, false},
       {3, 0, 2000, 2013, 4, false, true}, {3, 0, 106, 113, 4, false, false},
   };
   for (const Case& c : cases) {
