@@ -37,11 +37,10 @@ int launch_fused_free(void* const* user, int P, int op, int64_t n, int64_t strid
   std::memset(&a, 0, sizeof a);
   for (int x = 0; x < P; ++x) a.user[x] = user[x];
   const bool gaps = instances > 1 && stride != n;
-  const bool lines = rows_on_lines(user, P) && (!gaps || stride % 32 == 0);
   a.split = split ? 1 : 0;
   a.n = gaps ? n : instances * n;
   a.stride = stride;
-  FreeShape sh = free_shape(P, split, lines, tune, n, gaps ? stride - n : 0);
+  FreeShape sh = free_shape(P, split, rows_on_lines(user, P), tune, n, gaps ? stride - n : 0);
   a.gpi = (a.n + sh.V - 1) / sh.V;
   a.groups = (gaps ? instances : 1) * a.gpi;
   a.gaps = !gaps ? 0 : a.groups + kBlock < int64_t(UINT32_MAX) ? 1 : 2;

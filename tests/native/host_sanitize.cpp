@@ -656,30 +656,33 @@ static void int32_split_choice() {
   }
 }
 
-// int32 launches with gaps: cached up to 640 MiB of traffic, and above it where an
-// instance is short and less than a line follows it; a launch without gaps streams
-// on the lines from the size that `big` states.
+// int32 launches with gaps: up to 16 ranks cached up to 640 MiB of traffic, and
+// above it where an instance is short and less than a line follows it; from 17 ranks
+// nontemporal where the gaps are multiples of 16 elements.  A launch without gaps
+// streams on the lines from the size that `big` states.
 static void int32_gap_accesses() {
   struct Case {
     int P;
     int64_t mib, n, gap;
-    bool lines, nt;
+    bool rows, nt;
   };
   const Case cases[] = {
+      {24, 200, 1000, 24, true, false}, {24, 200, 208, 16, true, true},   {24, 200, 1001, 32, true, true},
+      {24, 800, 88, 8, true, false},    {127, 200, 2304, 64, true, true}, {24, 200, 208, 16, false, false},
       {4, 200, 1000, 24, true, false}, {16, 500, 1000, 24, true, false}, {16, 640, 1000, 24, true, true},
       {2, 639, 2304, 64, true, false}, {3, 800, 1000, 1, false, true},   {3, 200, 1000, 1, false, false},
       {8, 800, 1000, 1, false, false}, {16, 800, 88, 8, true, false},    {16, 800, 88, 40, true, true},
-      {16, 800, 192, 8, true, true},   {16, 200, 1000, 0, true, true},   {127, 800, 1000, 24, true, false},
+      {16, 800, 192, 32, true, true},  {16, 200, 1000, 0, true, true},   {127, 800, 1000, 24, true, false},
   };
   for (const Case& c : cases) {
     ar::FusedTuning t{};
     t.bytes = c.mib << 20;
     t.nt = -1;
     t.big = 1;
-    EXPECT(ar::free_shape(c.P, false, c.lines, t, c.n, c.gap).nt == c.nt, "int32 accesses: P=%d %lld MiB n=%lld gap %lld",
+    EXPECT(ar::free_shape(c.P, false, c.rows, t, c.n, c.gap).nt == c.nt, "int32 accesses: P=%d %lld MiB n=%lld gap %lld",
            c.P, (long long)c.mib, (long long)c.n, (long long)c.gap);
     t.big = 0;
-    EXPECT(!ar::free_shape(c.P, false, c.lines, t, c.n, c.gap).nt, "int32 accesses: small calls are cached");
+    EXPECT(!ar::free_shape(c.P, false, c.rows, t, c.n, c.gap).nt, "int32 accesses: small calls are cached");
   }
 }
 
