@@ -190,6 +190,14 @@ struct FusedArgs {
   FastDiv ndiv;             // n, for gaps between instances (set by the launcher)
 };
 
+// Nontemporal accesses of a latency-optimal launch with one column per lane that
+// the host would stream: not off the lines from five ranks up (stream_nt's reason).
+// Up to four they are the faster ones there too: P = 2, 140 MB of traffic 27.7 us
+// against 30.4 cached, P = 4 28.6 against 29.4.
+inline bool lo_nt(const FusedArgs& a, int P, bool nt) {
+  return nt && (P <= 4 || a.tune.nt == 1 || rows_on_lines(a.user, P));
+}
+
 // Column kernels: wave tile t -> (instance, block, 64 columns of the block).
 // The rank table is stored twice over (user[x] == user[x + P]) so that the
 // ranks b, b+1, ..., b+P-1 of a rotation are consecutive entries.

@@ -132,7 +132,7 @@ int launch_fused_p(const FusedArgs& args, int mode, bool nt, int grid, hipStream
       }
     }
     const dim3 g(grid);
-    if (nt && (lines || a.tune.nt == 1)) hipLaunchKernelGGL((fused_lo_kernel<P, OP, 1, true, false>), g, blk, a.lds, s, a);
+    if (lo_nt(a, P, nt)) hipLaunchKernelGGL((fused_lo_kernel<P, OP, 1, true, false>), g, blk, a.lds, s, a);
     else hipLaunchKernelGGL((fused_lo_kernel<P, OP, 1, false, false>), g, blk, a.lds, s, a);
   } else if (mode == 2) {
     if (a.groups <= int64_t(UINT32_MAX)) a.ndiv = make_fastdiv(uint32_t(a.n));

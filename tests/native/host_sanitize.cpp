@@ -751,6 +751,23 @@ static void flat_accesses() {
   }
 }
 
+// Latency-optimal launches: nontemporal off the lines up to four ranks, or forced.
+static void lo_accesses() {
+  for (int P = 2; P <= 16; ++P)
+    for (uintptr_t misalign : {uintptr_t(0), uintptr_t(4)})
+      for (int forced = -1; forced <= 1; ++forced) {
+        ar::FusedArgs a;
+        std::memset(&a, 0, sizeof a);
+        const std::vector<void*> bufs = fake_buffers(P, 1 << 20);
+        for (int x = 0; x < P; ++x) a.user[x] = bufs[size_t(x)];
+        a.user[1] = reinterpret_cast<char*>(a.user[1]) + misalign;
+        a.tune.nt = forced;
+        EXPECT(ar::lo_nt(a, P, forced != 0) == (forced == 1 || (forced < 0 && (P <= 4 || misalign == 0))) &&
+                   !ar::lo_nt(a, P, false),
+               "latency-optimal accesses: P=%d misalign %zu AR_FUSED_NT=%d", P, size_t(misalign), forced);
+      }
+}
+
 // Block tiles (AR_FUSED_ROTATE=0): the order of flat columns.  Plans read the
 // variable when they are created: single-threaded only.
 static void broadcast_block_order() {
@@ -1039,6 +1056,7 @@ int main(int argc, char** argv) {
       int32_split_choice();
       int32_gap_accesses();
       flat_accesses();
+      lo_accesses();
     });
     for (int t = 0; t < nt; ++t) th.emplace_back([t, nt, pmax, &counts] { counts[size_t(t)] = sweep(1 + t, nt, pmax); });
     for (std::thread& x : th) x.join();
@@ -1051,6 +1069,7 @@ int main(int argc, char** argv) {
     int32_split_choice();
     int32_gap_accesses();
     flat_accesses();
+    lo_accesses();
     broadcast_order_override();
     broadcast_overrides_with_gaps();
     broadcast_block_order();
