@@ -276,7 +276,8 @@ def _ptr_table(plan: int, rank_buffers, batch: int = 1, instance_stride: int | N
         st = ar_plan_stats(plan)
         info = _PLAN_INFO[plan] = (st.P, st.n, None)
     P, n, dt = info
-    addrs = [b.data_ptr() if isinstance(b, torch.Tensor) else int(b) for b in bufs]
+    raw = set(map(type, bufs)) == {int}  # addresses only: nothing to check rank by rank
+    addrs = bufs if raw else [b.data_ptr() if isinstance(b, torch.Tensor) else int(b) for b in bufs]
     if len(bufs) != P:
         raise ArError(AR_ERR_INVALID_ARG, "rank buffers", "the plan has P=%d ranks, got %d buffers" % (P, len(bufs)))
     if batch < 1:
@@ -286,7 +287,7 @@ def _ptr_table(plan: int, rank_buffers, batch: int = 1, instance_stride: int | N
     want = _TORCH_DTYPE.get(dt)
     dev = None
     storage_elems = {}
-    for x, b in enumerate(bufs):
+    for x, b in enumerate(() if raw else bufs):
         if not isinstance(b, torch.Tensor):
             continue
         if extent > 0:
@@ -329,11 +330,15 @@ def _native(plan: int, rank_buffers, batch: int, instance_stride: int, stream, w
     info = _PLAN_INFO.get(plan)
     if info is None or not torch.cuda.is_initialized():  # no GPU tensor exists before
         return False
+    if type(rank_buffers) is list and rank_buffers and type(rank_buffers[0]) is int:  # raw addresses
+        return False
     dev = torch._C._cuda_getDevice()
     if stream is None:
         handle = torch._C._cuda_getCurrentRawStream(dev)
     elif isinstance(stream, torch.cuda.Stream):
         handle = stream.cuda_stream
+    elif type(stream) is int:
+        handle = stream
     else:
         return False
     st = _bind_execute(plan, info, rank_buffers, batch, instance_stride, dev, handle, which)

@@ -60,6 +60,37 @@ def test_accepted_forms(form):
 
 
 @pytest.mark.gpu
+def test_a_stream_handle_takes_the_native_path(monkeypatch):
+    """A stream given as its handle is no reason to check every rank in Python."""
+    plan = ar.Plan(P, N, "float32", "sum", 4)
+    x = np.random.default_rng(8).normal(size=(P, 2, N)).astype(np.float32)
+    X = torch.from_numpy(x).cuda()
+    rows = list(X.unbind(0))
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    monkeypatch.setattr(ar, "_ptr_table", lambda *a, **k: pytest.fail("the Python path ran"))
+    plan.batched(rows, 1, N, stream=s.cuda_stream)
+    plan.batched([r[1] for r in rows], 1, N, stream=0)
+    torch.cuda.synchronize()
+    assert np.array_equal(X.cpu().numpy().view(np.uint32), oracle.allreduce_batched(x, 4, "sum").view(np.uint32))
+    plan.close()
+
+
+def test_tables_of_raw_addresses():
+    plan = ar.Plan(P, N, "float32", "sum", 4)
+    addrs = [4096 * (i + 1) for i in range(P)]
+    for form in (addrs, tuple(addrs), iter(addrs), [np.int64(a) for a in addrs], [True] + addrs[1:]):
+        want = [int(form[0])] + addrs[1:] if isinstance(form, list) else addrs
+        assert list(ar._ptr_table(plan.handle, form)) == want
+    for bad in (addrs[:-1], addrs + [4096], []):
+        with pytest.raises(ar.ArError, match="P=5 ranks"):
+            ar._ptr_table(plan.handle, bad)
+    with pytest.raises(ar.ArError, match="batch"):
+        ar._ptr_table(plan.handle, addrs, 0, N)
+    plan.close()
+
+
+@pytest.mark.gpu
 def test_refused_buffers_name_the_fault_each_time():
     plan = ar.Plan(P, N, "float32", "sum", 4)
     rows = [torch.zeros(N, device="cuda") for _ in range(P)]
