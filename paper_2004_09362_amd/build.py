@@ -177,7 +177,8 @@ def kernel_families(kernel: str) -> list[str]:
         for prefix, fam in (("step_kernel", "step"), ("fused_lo_kernel", "lo"), ("fused_bo_kernel", "col"),
                             ("fused_mid_kernel", "col"), ("fused_rot_kernel", "col"), ("fused_xor_kernel", "group"),
                             ("fused_ring_kernel", "group"), ("fused_free_kernel", "free"),
-                            ("fused_small_kernel", "small"), ("broadcast", "bcast")):
+                            ("fused_small_kernel", "small"), ("fused_wide_kernel", "col"),
+                            ("fused_xor_wide_kernel", "group"), ("broadcast", "bcast")):
             if part.startswith(prefix):
                 out.append(fam)
                 break

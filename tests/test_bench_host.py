@@ -2,6 +2,7 @@
 import csv
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -98,6 +99,17 @@ def test_kernel_families_cover_every_source():
     assert {b.kernel_families(k)[0] for k in ("step_kernel<k=10>", "fused_lo_kernel<P=12>", "fused_bo_kernel<P=24>",
                                               "fused_mid_kernel<P=37>", "fused_xor_kernel<P=32,R=0>",
                                               "fused_ring_kernel")} == {"step", "lo", "col", "group"}
+    # every kernel of the sources has a family, the one of its own file
+    kernels = {}
+    for fam, files in b.FAMILIES.items():
+        for f in files:
+            with open(os.path.join(b.CSRC, f), encoding="utf-8") as fh:
+                for name in re.findall(r"__global__[^;{]*?\bvoid\s+(\w+)\s*\(", fh.read()):
+                    kernels[name] = fam
+    assert {"fused_wide_kernel", "fused_xor_wide_kernel", "fused_small_kernel", "broadcast_stream_kernel"} <= set(kernels)
+    for name, fam in kernels.items():
+        if name != "step_merged_kernel":  # bench.py reports both step kernels as step_kernel
+            assert b.kernel_families(name + "<P=8>") == [fam], name
     assert b.kernel_families("fused_bo_kernel<P=127>+broadcast") == ["col", "bcast"]
     assert b.kernel_families("fused_bo_kernel<P=127>+broadcast_stream") == ["col", "bcast"]
     assert b.source_hash(["col", "bcast"]) != b.source_hash("col")
