@@ -9,8 +9,11 @@ the length from which a lane may hold part of a group), rows on and off the
 the ends of the type, so sums wrap round.
 """
 import pytest
+import torch
 
+from paper_2004_09362_amd import ar
 from test_gpu_line_grids import check
+from test_gpu_parity import DEV, note
 
 pytestmark = pytest.mark.gpu
 
@@ -34,9 +37,31 @@ def test_any_int32_plan(P, split, nt, monkeypatch):
         check(P, 777, 2 * L(P) - 1, dtype="int32", op="max", group="xor")
 
 
-@pytest.mark.parametrize("P", [5, 24, 100])
-def test_split_by_size_and_one_launch_agree(P):
-    """Rank instances just below and at the size from which int32 plans of
-    12 ranks and more split, rows off the lines."""
-    for n in ((1 << 20) - 1, 1 << 20):
-        check(P, n, L(P), lead=1, dtype="int32", op="max")
+def launches(P, n, B, pitch, k):
+    """Launches of one call on rows `pitch` elements apart, B instances back to back."""
+    X = torch.zeros((P, pitch), dtype=torch.int32, device=DEV)
+    plan = ar.Plan(P, n, "int32", "max", k)
+    ms = plan.timed(list(X.unbind(0)), B, n)
+    plan.close()
+    return len(ms)
+
+
+@pytest.mark.parametrize("P,k", [(16, 4), (17, 5), (24, 10), (100, 14)])
+def test_split_by_size_and_one_launch_agree(P, k):
+    """Calls just below and at the size from which int32 plans of 17 ranks and
+    more split, rows off the lines (288 MiB over all ranks): one instance, and
+    a batch of short ones, whose size is that of all its instances."""
+    least = (288 << 20) // 4 // P
+    for n, B in ((least - 1, 1), (least, 1), (106, least // 106), (106, least // 106 + 1)):
+        want = 2 if P >= 17 and n * B >= least else 1
+        note("int32 split P=%d n=%d B=%d k=%d" % (P, n, B, k))
+        assert launches(P, n, B, -(-n * B // 32) * 32 + 1, k) == want, (P, n, B)
+        if B > 1 or n == least:
+            check(P, n, k, B=B, lead=1, dtype="int32", op="max")
+
+
+@pytest.mark.parametrize("P,mib", [(24, 200), (33, 128), (127, 128)])
+def test_split_size_on_the_lines(P, mib):
+    least = (mib << 20) // 4 // P
+    for n, B in ((least - 1, 1), (least, 1), (106, least // 106), (106, least // 106 + 1)):
+        assert launches(P, n, B, -(-n * B // 32) * 32, L(P)) == (2 if n * B >= least else 1), (P, n, B)

@@ -1,6 +1,6 @@
 """fp32 calls of few columns at many ranks, on the GPU, bit for bit against the
 oracle: the kernel that deals the ranks out over a workgroup's waves, at every
-step count, on both sides of a workgroup's 32 columns, of the ranks a wave
+step count, on both sides of a workgroup's 16 columns, of the ranks a wave
 covers and of the size up to which it is taken; batches with and without
 gaps, blocks of no, one and several elements, and signed zeros, whose maximum
 shows every combination's operand order."""
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 def test_every_step_count(P):
     L = (P - 1).bit_length()
     for k in range(L, 2 * L + 1):
-        for n, B, gap, lead in ((1, 1, 0, 0), (31, 1, 0, 3), (106, 1, 0, 1), (P + 1, 3, 0, 0), (33, 5, 7, 2),
+        for n, B, gap, lead in ((1, 1, 0, 0), (15, 1, 0, 1), (16, 1, 0, 0), (17, 1, 0, 2), (31, 1, 0, 3), (106, 1, 0, 1), (P + 1, 3, 0, 0), (33, 5, 7, 2),
                                 (4095, 1, 0, 0), (4097, 1, 0, 0), (1024, 4, 1, 0)):
             check(P, n, k, B=B, gap=gap, lead=lead, op=("sum", "max")[(n + k) % 2])
 

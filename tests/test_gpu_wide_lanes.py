@@ -52,7 +52,7 @@ def test_few_ranks_split(P, split, monkeypatch):
         check(P, P * 1024 * int(split) + 5, 2 * L(P), lead=lead)
 
 
-@pytest.mark.parametrize("nt", [None, "1"])
+@pytest.mark.parametrize("nt", [None, "0", "1"])
 @pytest.mark.parametrize("P", [13, 24, 37, 48, 100, 127])
 def test_more_ranks_off_the_lines(P, nt, monkeypatch):
     if nt is not None:
