@@ -116,9 +116,9 @@ constexpr int64_t kPackMaxLen = 64;
 // kRotShiftedSmallMaxBytes per rank: 1-5% less time at P = 24, 33, 34, 37,
 // 47 and 48 with 8-32 MB per rank (the prime_sweep shape, P = 37 at 16 MB:
 // 4-5% at k = 7-11), 1-10% more at 64 MB; at P = 64-93 within 2.4% either
-// way up to 32 MB.  Shifted max plans take this second rule as well (their
-// rank-slot kernels exist at P = 24-48 only): 4-7% less time at P = 37 and
-// 48 with 16 MB per rank, 2.6% more at P = 24 with 32 MB.
+// way up to 32 MB.  Shifted max plans take this second rule as well: 4-7%
+// less time at P = 37 and 48 with 16 MB per rank, 2.6% more at P = 24 with
+// 32 MB.
 constexpr int32_t kRotShiftedMinP = 97;
 constexpr int32_t kRotShiftedSmallMinP = 24, kRotShiftedSmallMaxP = 48;
 constexpr int64_t kRotShiftedSmallMaxBytes = int64_t(32) << 20;
@@ -838,11 +838,15 @@ std::string plan_text(const ar_plan* pl) {
                     (long long)s.hbm_blocks, s.uses_scratch ? "yes" : "no"));
   static const char* const kKind[] = {"none", "latency-optimal, registers", "cyclic butterfly columns", "XOR group columns",
                                       "Ring columns"};
-  add(std::snprintf(line, sizeof line,
-                    "  fused: %s; flat short blocks %s; split %s; caps %d/%d; path %s\n",
-                    kKind[pl->fused_kind], pl->fused_flat ? "yes" : "no", pl->fused_split ? "yes" : "no", pl->fused_cap,
-                    pl->bcast_cap,
-                    pl->path == AR_PATH_STEPWISE ? "stepwise" : pl->path == AR_PATH_FUSED ? "fused" : "auto"));
+  const char* const path =
+      pl->path == AR_PATH_STEPWISE ? "stepwise" : pl->path == AR_PATH_FUSED ? "fused" : "auto";
+  if (pl->any_order)  // one kernel whatever the plan, shaped and split call by call
+    add(std::snprintf(line, sizeof line, "  fused: int32 columns, any order; one instance split %s; path %s\n",
+                      pl->fused_split ? "yes" : "no", path));
+  else
+    add(std::snprintf(line, sizeof line, "  fused: %s; flat short blocks %s; split %s; caps %d/%d; path %s\n",
+                      kKind[pl->fused_kind], pl->fused_flat ? "yes" : "no", pl->fused_split ? "yes" : "no",
+                      pl->fused_cap, pl->bcast_cap, path));
   static const char* const kPhase[] = {"reduce", "distribute", "local copy"};
   static const char* const kRange[] = {"copy", "reduce", "reduce2"};
   for (size_t i = 0; i < s.launches.size(); ++i) {
@@ -951,8 +955,9 @@ ar_status create_plan(int32_t P, int64_t n, ar_dtype dtype, ar_op op, int32_t k_
                       (pl->fused_kind == kFusedCol && pl->s.r < pl->s.L);
     // max: the rank-slot kernel's bandwidth-optimal fold and Ring, its
     // shifted plans at P = kRotMaxShiftedMinP-kRotMaxShiftedMaxP (elsewhere
-    // they keep block or packed tiles, saving their instantiations), and the
-    // XOR group, whose flat kernel then takes each lane's block
+    // block tiles, or on short blocks the rank slots' cached form, which
+    // launch_fused_mid chooses), and the XOR group, whose flat kernel then
+    // takes each lane's block
     const bool max_mid_p = pl->s.P >= ar::kRotMaxShiftedMinP && pl->s.P <= ar::kRotMaxShiftedMaxP;
     const bool op_ok = pl->op == AR_SUM || pl->fused_kind == kFusedRing || pl->fused_kind == kFusedXor ||
                        (pl->fused_kind == kFusedCol && (pl->s.r == 0 || max_mid_p));

@@ -69,6 +69,15 @@ def test_dump_matches_plan_and_tables(P, k, group, schedule):
         assert parse_launch_line(lines[3 + i]) == ranges, (P, k, i)
 
 
+@pytest.mark.parametrize("P,k,group,schedule", [(7, 5, "cyclic", "butterfly"), (12, 4, "cyclic", "butterfly"),
+                                                (8, 4, "xor", "butterfly"), (5, 8, "cyclic", "ring")])
+def test_dump_names_the_path_of_int32_plans(P, k, group, schedule):
+    line = ar.Plan(P, 1000, "int32", "max", k, group=group, schedule=schedule).dump().split("\n")[2]
+    assert line == "  fused: int32 columns, any order; one instance split no; path auto"
+    line = ar.Plan(P, 1000, "float32", "max", k, group=group, schedule=schedule).dump().split("\n")[2]
+    assert "any order" not in line and "caps" in line
+
+
 def test_dump_truncates_into_small_buffers():
     plan = ar.Plan(7, 1000, "int32", "max", 4)
     full = plan.dump()
