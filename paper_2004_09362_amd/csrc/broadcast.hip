@@ -168,17 +168,20 @@ __global__ __launch_bounds__(kStreamBlock) void broadcast_stream_kernel(const Co
 // order, so that four are resident on a CU, where eight fit: with fewer
 // stores in flight each XCD's sweep stays in fewer DRAM rows.  P = 127 at 72 MB
 // per rank: 7.38 against 7.16 TB/s (rows off the lines 7.19 against 6.79),
-// P = 128 at 64 MB 7.37 against 7.15; three a CU: 6.4.  Interleaved chunks
-// (one sweep for the whole chip) and copies with gaps ran within 2% either
-// way or slower with it.
-constexpr uint32_t kCopyLds = 39 * 1024;
+// P = 128 at 64 MB 7.37 against 7.15; three a CU: 6.4.  Interleaved chunks (one
+// sweep for the whole chip) on the lines keep six: whole calls of 2-16 MiB per
+// rank, P = 33-127, took 0.967-1.009 of the time that an earlier copy with more
+// index arithmetic per workgroup took, without a cap 0.96-1.03 (100 ranks at 2 MiB 1.03,
+// 64 at 5 MiB 1.017).  Off the lines, and with gaps, they ran within 2% either way
+// or slower with a cap.
+constexpr uint32_t kCopyLds = 39 * 1024, kCopyInterleavedLds = 26 * 1024;
 
 }  // namespace
 
 int launch_copy(const CopyArgs& a, uint32_t grid, bool nt, bool gap, bool lines, void* stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const dim3 g(grid), blk(kStreamBlock);
-  const uint32_t lds = a.mask != 0 && !gap ? kCopyLds : 0;
+  const uint32_t lds = gap ? 0 : a.mask != 0 ? kCopyLds : lines ? 0 : kCopyInterleavedLds;
 #define AR_COPY(GAP, LINES)                                                                               \
   do {                                                                                                    \
     if (nt) hipLaunchKernelGGL((broadcast_stream_kernel<true, GAP, LINES>), g, blk, lds, s, a);             \
