@@ -512,10 +512,6 @@ int launch_fused_bo(const ColArgs& a, int dtype, int op, bool nt, int grid, void
   return int(hipGetLastError());
 }
 
-}  // namespace ar
-
-namespace ar {
-
 template <int P>
 int launch_fused_mid(const ColArgs& a, int dtype, int op, bool nt, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.instances, a.split != 0, a.tune, stream);

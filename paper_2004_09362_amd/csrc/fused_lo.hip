@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void fused_lo_kernel(const FusedArgs a) {
 // 5.15 / 5.8, P = 8 4.6 / 5.8); else one, with which P = 4-12 on the lines streamed
 // 4-9% faster.  Accesses off the lines are cached from five ranks up
 // (stream_nt's reason).
-template <int P, typename T, int OP>
+template <int P, int OP>
 int launch_fused_p(const FusedArgs& args, int mode, bool nt, int grid, hipStream_t s) {
   FusedArgs a = args;
   const dim3 blk(kBlock);
@@ -143,11 +143,11 @@ int launch_fused_p(const FusedArgs& args, int mode, bool nt, int grid, hipStream
   return int(hipGetLastError());
 }
 
-template <typename T, int OP>
-int launch_fused_t(const FusedArgs& a, int P, int mode, bool nt, int grid, hipStream_t s) {
+template <int OP>
+int launch_fused_op(const FusedArgs& a, int P, int mode, bool nt, int grid, hipStream_t s) {
   switch (P) {
 #define AR_LO_CASE(PP) \
-  case PP: return launch_fused_p<PP, T, OP>(a, mode, nt, grid, s);
+  case PP: return launch_fused_p<PP, OP>(a, mode, nt, grid, s);
     AR_LO_CASE(2) AR_LO_CASE(3) AR_LO_CASE(4) AR_LO_CASE(5) AR_LO_CASE(6) AR_LO_CASE(7) AR_LO_CASE(8)
     AR_LO_CASE(9) AR_LO_CASE(10) AR_LO_CASE(11) AR_LO_CASE(12) AR_LO_CASE(13) AR_LO_CASE(14)
     AR_LO_CASE(15) AR_LO_CASE(16)
@@ -161,7 +161,7 @@ int launch_fused_t(const FusedArgs& a, int P, int mode, bool nt, int grid, hipSt
 int launch_fused_lo(const FusedArgs& a, int P, int dtype, int op, int mode, bool nt, int grid, void* stream) {
   if (dtype == 0) return launch_fused_free(a.user, P, op, a.n, a.stride, a.batch, false, a.tune, stream);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  return op == 0 ? launch_fused_t<float, 0>(a, P, mode, nt, grid, s) : launch_fused_t<float, 1>(a, P, mode, nt, grid, s);
+  return op == 0 ? launch_fused_op<0>(a, P, mode, nt, grid, s) : launch_fused_op<1>(a, P, mode, nt, grid, s);
 }
 
 }  // namespace ar
