@@ -36,22 +36,23 @@ struct FreeShape {
 //     own bytes, on / off the lines: 8-byte lanes at three, P = 24 6.7 / 6.3,
 //     P = 32 6.55 / 6.2, P = 48 6.5 / 6.2; 4-byte lanes P = 64 6.5 / 5.9 (8-byte
 //     6.3 / 5.9), P = 127 6.5 / 5.5.
-// With gaps a lane's accesses cover parts of lines.  From 17 ranks nontemporal
-// where the gaps are multiples of 16 elements, which leave whole half lines
-// (nontemporal / cached on buffers that alternate beyond the caches, P = 24: 80 at
-// stride 96 0.80-0.88, 208 at 224 0.80-0.85, 1000 at 1032 0.81-0.91; 88 at 96 1.2-1.37, 1000
-// at 1008 1.02-1.14), cached elsewhere.  Up to 16 ranks cached up to kGapNtBytes: on
-// one set of buffers, which the caches hold to a good part, 1000 at stride 1024 took,
-// nontemporal / cached, at 160-460 MB of traffic, P = 4 1.33-1.42, P = 16 1.38-1.55, at 600
-// MB 1.06, 1.17, at 800 MB 0.93, 0.96 (on alternating ones 0.9-0.98 throughout), 2304 at
-// 2368 1.25, 1.3 and 0.89, 0.97; and above it where short instances leave less than a
-// line between them (88 at stride 96: 1.3 at 800 MB).
+// With gaps a lane's accesses cover parts of lines, except where the gaps are
+// multiples of 16 elements, which leave whole half lines.  There launches from 17
+// ranks are nontemporal, as are those without gaps (on buffers that alternate beyond
+// the caches, nontemporal / cached, P = 24: 80 at stride 96 0.80-0.88, 208 at 224
+// 0.80-0.85, 1000 at 1032 0.81-0.91), and up to 16 ranks those from kGapNtBytes (208 at 224
+// 0.74-0.83, 1008 at 1024 0.82-0.9, 2304 at 2368 0.85-0.95): one set of buffers, which
+// the caches hold to a good part up to 600 MB of traffic, then takes 1.2-1.7 of the
+// cached time, below kGapNtBytes up to 1.9.  Other gaps: cached from 17 ranks (88 at 96
+// 1.2-1.37, 1000 at 1008 1.02-1.14); up to 16 nontemporal from kGapNtBytes and 512
+// elements where every instance starts on a line (1000 at 1024 0.88-0.98), or at four
+// ranks and fewer (1000 at 1008 0.94-0.97), else cached (88 at 96 1.07-1.29).
 // Calls below kFusedNtThresholdBytes (not `big`) live in the caches: ordinary
 // accesses; and below kTightCapBytes the tight caps leave too few waves to
 // hide latency behind (P = 8 at 16 MB per rank: 52 us at six workgroups a CU,
 // 56 at two; P = 13 at 16 MB: 77 us with 4-byte lanes at four, 85 with 8-byte
 // lanes at two).
-constexpr int64_t kGapNtBytes = int64_t(640) << 20;
+constexpr int64_t kGapNtBytes = int64_t(256) << 20;
 // rows: the rank buffers start on 128-byte lines.  gap: elements between two
 // instances, 0 for one instance or none between them.
 inline FreeShape free_shape(int P, bool split, bool rows, const FusedTuning& tune, int64_t n, int64_t gap) {
@@ -80,8 +81,11 @@ inline FreeShape free_shape(int P, bool split, bool rows, const FusedTuning& tun
     else if (s.V == 2) cap = P <= 4 ? 4 : P <= 8 ? 2 : 1;
     else cap = P <= 6 ? 0 : P <= 16 ? 2 : P <= 64 || gaps ? 1 : 0;
     s.nt = lines ? P <= 65 : s.V == 4 && P <= 4;
-    if (gaps)
-      s.nt = P >= 17 ? rows && gap % 16 == 0 : s.nt && tune.bytes >= kGapNtBytes && (n >= 192 || gap >= 32);
+    if (gaps) {
+      const bool large = tune.bytes >= kGapNtBytes;
+      if (rows && gap % 16 == 0) s.nt = P >= 17 || large;
+      else s.nt = s.nt && P <= 16 && large && n >= 512;
+    }
   }
   s.nt = s.nt && tune.big != 0;
   s.lds = cap_lds_bytes(cap);

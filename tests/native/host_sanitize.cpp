@@ -656,10 +656,10 @@ static void int32_split_choice() {
   }
 }
 
-// int32 launches with gaps: up to 16 ranks cached up to 640 MiB of traffic, and
-// above it where an instance is short and less than a line follows it; from 17 ranks
-// nontemporal where the gaps are multiples of 16 elements.  A launch without gaps
-// streams on the lines from the size that `big` states.
+// int32 launches with gaps: nontemporal where the gaps are multiples of 16
+// elements, up to 16 ranks from 256 MiB of traffic; behind other gaps up to 16 ranks
+// from there and 512 elements, on the lines or at four ranks and fewer.  A launch
+// without gaps streams on the lines from the size that `big` states.
 static void int32_gap_accesses() {
   struct Case {
     int P;
@@ -667,12 +667,12 @@ static void int32_gap_accesses() {
     bool rows, nt;
   };
   const Case cases[] = {
-      {24, 200, 1000, 24, true, false}, {24, 200, 208, 16, true, true},   {24, 200, 1001, 32, true, true},
-      {24, 800, 88, 8, true, false},    {127, 200, 2304, 64, true, true}, {24, 200, 208, 16, false, false},
-      {4, 200, 1000, 24, true, false}, {16, 500, 1000, 24, true, false}, {16, 640, 1000, 24, true, true},
-      {2, 639, 2304, 64, true, false}, {3, 800, 1000, 1, false, true},   {3, 200, 1000, 1, false, false},
-      {8, 800, 1000, 1, false, false}, {16, 800, 88, 8, true, false},    {16, 800, 88, 40, true, true},
-      {16, 800, 192, 32, true, true},  {16, 200, 1000, 0, true, true},   {127, 800, 1000, 24, true, false},
+      {24, 200, 208, 16, true, true},    {24, 200, 1001, 32, true, true},  {127, 200, 2304, 64, true, true},
+      {24, 200, 208, 16, false, false},  {24, 800, 1000, 24, true, false}, {24, 800, 88, 8, true, false},
+      {16, 255, 208, 16, true, false},   {16, 256, 208, 16, true, true},   {8, 300, 104, 32, true, true},
+      {4, 255, 1000, 24, true, false},   {16, 256, 1000, 24, true, true},  {16, 800, 500, 12, true, false},
+      {8, 800, 88, 8, true, false},      {3, 800, 1000, 1, false, true},   {3, 800, 500, 4, false, false},
+      {8, 800, 1000, 1, false, false},   {16, 200, 1000, 0, true, true},   {127, 800, 1000, 24, true, false},
   };
   for (const Case& c : cases) {
     ar::FusedTuning t{};
