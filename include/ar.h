@@ -211,8 +211,8 @@ typedef struct {
                                         at least 2 MiB (AR_BCAST_STREAM overrides the
                                         size rule), for rank buffers on 128-byte lines
                                         without gaps between instances and, from 128 MiB
-                                        over all ranks (64 MiB below 48 ranks), at any
-                                        alignment and with gaps no
+                                        over all ranks (64 MiB below 48 ranks) or up to
+                                        64 KiB per rank, at any alignment and with gaps no
                                         wider than an instance (a multiple of 16
                                         elements: 3/8 of one, 1/8 or 1/16 for instances
                                         below 512 elements; of 32 with a stride that is

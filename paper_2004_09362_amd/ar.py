@@ -330,8 +330,6 @@ def _native(plan: int, rank_buffers, batch: int, instance_stride: int, stream, w
     info = _PLAN_INFO.get(plan)
     if info is None or not torch.cuda.is_initialized():  # no GPU tensor exists before
         return False
-    if type(rank_buffers) is list and rank_buffers and type(rank_buffers[0]) is int:  # raw addresses
-        return False
     dev = torch._C._cuda_getDevice()
     if stream is None:
         handle = torch._C._cuda_getCurrentRawStream(dev)

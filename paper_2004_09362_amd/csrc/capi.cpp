@@ -437,7 +437,7 @@ bool call_splits(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t st
   return free_splits(pl->s.P, n, batch, on_lines, gaps);
 }
 
-constexpr int64_t kCopyFewOddBytes = int64_t(64) << 20;
+constexpr int64_t kCopyFewOddBytes = int64_t(64) << 20, kCopyTinyBytes = int64_t(64) << 10;
 
 struct CopyCall {
   ar::CopyArgs a;
@@ -490,7 +490,11 @@ bool copy_call(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t stri
   // 1.0-1.4 / 1.05-1.2, at 96-127 MiB 1.0-1.2 / 1.0-1.1; below 48 ranks, whose reducing
   // launches stream past the caches, 1.04-1.08 / 0.83-0.97 at 64 MiB; from
   // kFusedNtThresholdBytes on 0.56-0.93.
-  if (mode < 0 && c->lines && int64_t(P) * n * batch * 4 < (P < 48 ? kCopyFewOddBytes : kFusedNtThresholdBytes))
+  // Spans of up to kCopyTinyBytes again by destinations: a column's P - 1 stores one
+  // after the other are then most of the call (P = 127, 106 columns 8.2 us against 11.9;
+  // at 64 KiB per rank 0.88-1.0 at P = 33-127, at 128 KiB 0.97-1.19).
+  if (mode < 0 && c->lines && span * 4 > kCopyTinyBytes &&
+      int64_t(P) * n * batch * 4 < (P < 48 ? kCopyFewOddBytes : kFusedNtThresholdBytes))
     return false;
   // The slices of a call are evened out and rounded up to the XCD count: a
   // short last slice in regions leaves most XCDs idle.

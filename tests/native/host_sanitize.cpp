@@ -559,6 +559,9 @@ static void broadcast_choice() {
       {40, 1000, 12, AR_GROUP_CYCLIC, 420, 3, 0, "broadcast_stream", 0},
       {40, 1000, 12, AR_GROUP_CYCLIC, 400, 0, 64, "broadcast", -1},
       {48, 1000, 12, AR_GROUP_CYCLIC, 420, 3, 0, "broadcast", -1},
+      {127, 106, 14, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 0},  // tiny calls by destinations
+      {64, 16384, 12, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast_stream", 0},
+      {64, 16385, 12, AR_GROUP_CYCLIC, 1, 0, 4, "broadcast", -1},
       // gaps on both sides of the width that the copy walks: other widths, multiples of 32 and of 16
       {64, 106, 12, AR_GROUP_CYCLIC, 8000, 106, 0, "broadcast_stream", 0},
       {64, 106, 12, AR_GROUP_CYCLIC, 8000, 107, 0, "broadcast", -1},
