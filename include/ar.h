@@ -183,12 +183,11 @@ typedef struct {
                                         kernel).  int32 plans, whose combinations give
                                         the same bits in any order, have one result at
                                         every k and split call by call for P >= 17: where
-                                        P * n * batch * e is at least 128 MiB (200 MiB
-                                        for P < 33) on 128-byte lines without gaps,
-                                        288 MiB otherwise (instances of 512 elements or
-                                        more off the lines; behind wide gaps from
-                                        P = 48).  This and hbm_bytes_fused
-                                        state one instance on the lines                  */
+                                        P * n * batch * e is at least 128 MiB (144 MiB
+                                        for P < 33), 288 MiB with gaps between the
+                                        instances (of 512 elements or more off the
+                                        128-byte lines; behind wide gaps from P = 48).
+                                        This and hbm_bytes_fused state one instance      */
   int32_t fused_flat;                /* FUSED path with short blocks (sums; max in the
                                         bandwidth-optimal, Ring and XOR plans), and on
                                         long blocks the AR_FUSED_ROTATE defaults: 1

@@ -41,22 +41,23 @@ constexpr int32_t kSplitMidMinP = 24;
 constexpr int64_t kSplitMidMinBytes = int64_t(32) << 20;
 // int32 calls (any k, group and schedule: one result) split from
 // kFreeSplitMinP ranks by the bytes of the call over all ranks, all instances
-// together.  On the 128-byte lines from kFreeSplitBytes, below kFreeSplitManyP
-// ranks from kFreeSplitFewBytes: one launch / split took at 128 MiB 1.0-1.18 (rows a
-// power of two apart 0.93-1.05), at 192 MiB and P = 17-28 1.03-1.14 (0.86-0.89), at
-// 256 MiB and more 1.0-1.35 (1.0-1.13); at 96 MiB 0.92-1.05, at 64 0.73-0.98.  From
-// kFreeSplitOddBytes off the lines or with
-// gaps between the instances (256 MiB 0.81-0.88, 320 1.05-1.22; batches of 2304 at
-// stride 2311, 254 MB 0.82-0.87, 384-512 MB 1.02-1.11).  Instances below
-// kFreeSplitMinGapped elements that start off the lines stay on one launch (106 at
-// stride 113: 0.87-1.09).  Behind gaps too wide for the destination-major copy the
-// tiled one pays from kFreeSplitTiledMinP ranks where its waves lie on half lines
-// (gaps of a multiple of 16; 48 at stride 80, P = 64 1.3) or instances are long (2304,
-// P = 37 0.95-1.0, P = 64 1.04, P = 127 1.1; 1000, P = 64 0.83).
+// together: from kFreeSplitBytes, below kFreeSplitManyP ranks from kFreeSplitFewBytes.
+// One launch / split, on one set of buffers and on buffers that alternate beyond the
+// caches, P = 17-127: on the 128-byte lines at 96 MiB 0.87-1.05 and 0.81-1.03, at 128
+// 0.98-1.18 and 1.02-1.25, at 256 and more 0.97-1.35 on both (rows a power of two
+// apart: P = 17 at 136 MiB 0.86 and 0.9, from 272 on 1.1); off them at 128-256 MiB
+// 0.79-0.95 and 1.09-1.4, from 320 on 1.03-1.4 on both.  With gaps between the
+// instances from kFreeSplitGapBytes (2304 at stride 2311, 254 MB 0.82-0.87 and
+// 0.84-1.14, 384-512 MB 1.02-1.11 and 0.98-1.11).  Instances below kFreeSplitMinGapped
+// elements that start off the lines stay on one launch (106 at stride 113: 0.87-1.09
+// and 0.8-0.96).  Behind gaps too wide for the destination-major copy the tiled one
+// pays from kFreeSplitTiledMinP ranks where its waves lie on half lines (gaps of a
+// multiple of 16; 48 at stride 80, P = 64 1.3) or instances are long (2304, P = 37
+// 0.95-1.0, P = 64 1.04, P = 127 1.1; 1000, P = 64 0.83).
 constexpr int32_t kFreeSplitMinP = 17, kFreeSplitTiledMinP = 48;
 constexpr int32_t kFreeSplitManyP = 33;
-constexpr int64_t kFreeSplitBytes = int64_t(128) << 20, kFreeSplitFewBytes = int64_t(200) << 20;
-constexpr int64_t kFreeSplitOddBytes = int64_t(288) << 20;
+constexpr int64_t kFreeSplitBytes = int64_t(128) << 20, kFreeSplitFewBytes = int64_t(144) << 20;
+constexpr int64_t kFreeSplitGapBytes = int64_t(288) << 20;
 constexpr int64_t kFreeSplitMinGapped = 512, kFreeSplitTiledMinLen = 2048;
 // Flat short-block sums in the rank-slot kernel (not the XOR group's) split
 // from this many ranks up: their single launch streams 5.0-5.6 TB/s there and
@@ -204,7 +205,7 @@ struct ar_plan {
   // allow; default: for blocks of up to kMergeMaxLen elements).
   int32_t nt_mode = -1, fused_nt_mode = -1, split_mode = -1, bcast_nt_mode = -1, bcast_stream_mode = -1;
   int32_t packed_mode = -1, rotate_mode = -1, merge_mode = -1;
-  bool fused_split = false;  // int32 plans: one instance on the lines (call_splits decides for a call)
+  bool fused_split = false;  // int32 plans: one instance (call_splits decides for a call)
   bool any_order = false;    // int32: combinations give the same bits in any order
   // Sums whose blocks hold at most kPackMaxLen elements run on flat columns
   // whenever the batch's columns fit in 32 bits: the cyclic butterfly plans
@@ -418,8 +419,8 @@ bool narrow_gaps(int64_t n, int64_t stride) {
 }
 
 // Whether int32 calls of this many bytes over all ranks split by default.
-bool free_splits(int32_t P, int64_t n, int64_t batch, bool on_lines, bool gaps) {
-  const int64_t least = !on_lines || gaps ? kFreeSplitOddBytes : P < kFreeSplitManyP ? kFreeSplitFewBytes : kFreeSplitBytes;
+bool free_splits(int32_t P, int64_t n, int64_t batch, bool gaps) {
+  const int64_t least = gaps ? kFreeSplitGapBytes : P < kFreeSplitManyP ? kFreeSplitFewBytes : kFreeSplitBytes;
   return P >= kFreeSplitMinP && n * batch >= least / 4 / P;
 }
 
@@ -428,13 +429,12 @@ bool call_splits(const ar_plan* pl, void* const* bufs, int64_t batch, int64_t st
   if (!pl->any_order || pl->split_mode >= 0) return pl->fused_split;
   const int64_t n = pl->s.n;
   const bool gaps = batch > 1 && stride != n;
-  const bool on_lines = ar::rows_on_lines(bufs, pl->s.P) && (!gaps || stride % 32 == 0);
   if (gaps && narrow_gaps(n, stride)) {
-    if (n < kFreeSplitMinGapped && !on_lines) return false;
+    if (n < kFreeSplitMinGapped && !(stride % 32 == 0 && ar::rows_on_lines(bufs, pl->s.P))) return false;
   } else if (gaps) {
     if (pl->s.P < kFreeSplitTiledMinP || (n < kFreeSplitTiledMinLen && (stride - n) % 16 != 0)) return false;
   }
-  return free_splits(pl->s.P, n, batch, on_lines, gaps);
+  return free_splits(pl->s.P, n, batch, gaps);
 }
 
 constexpr int64_t kCopyFewOddBytes = int64_t(64) << 20, kCopyTinyBytes = int64_t(64) << 10;
@@ -895,7 +895,7 @@ double model_seconds(const ar_plan* pl, const ar_model_params& mp, int64_t batch
   const ar::Schedule& s = pl->s;
   if (s.P < 2 || s.n == 0) return 0.0;
   if (path == AR_PATH_FUSED) {
-    const bool split = pl->any_order && pl->split_mode < 0 ? free_splits(s.P, s.n, batch, true, false) : pl->fused_split;
+    const bool split = pl->any_order && pl->split_mode < 0 ? free_splits(s.P, s.n, batch, false) : pl->fused_split;
     const double launches = split ? 2.0 : 1.0;
     const double bytes = double(int64_t(2) * s.P + (split ? 1 : 0)) * double(s.n) * 4.0 * double(batch);
     return launches * mp.fused_alpha + bytes / mp.fused_bytes_per_s;
@@ -983,7 +983,7 @@ ar_status create_plan(int32_t P, int64_t n, ar_dtype dtype, ar_op op, int32_t k_
   const int32_t split_min =
       rank_slots ? kFlatSplitMinP : (pl->s.n * 4 >= kSplitMidMinBytes ? kSplitMidMinP : kSplitMinP);
   const bool split_by_size =
-      pl->any_order ? free_splits(pl->s.P, pl->s.n, 1, true, false) : pl->s.P >= split_min;
+      pl->any_order ? free_splits(pl->s.P, pl->s.n, 1, false) : pl->s.P >= split_min;
   pl->fused_split = one_result && (pl->split_mode == 1 || (pl->split_mode < 0 && split_by_size));
   {
     const int32_t P = pl->s.P;

@@ -608,8 +608,7 @@ static void check_broadcast_case(const BcastCase& c) {
 }
 
 // int32 calls split by their own bytes: every k and schedule alike, batches by
-// all their instances, on both sides of the sizes for rows on the 128-byte lines
-// and off them, and with gaps.
+// all their instances, on both sides of the sizes without gaps and with them.
 static void int32_split_choice() {
   struct Case {
     int P;
@@ -621,9 +620,9 @@ static void int32_split_choice() {
       {16, int64_t(1) << 24, 1, 0, 0, 1},    // below 17 ranks
       {17, int64_t(1) << 20, 1, 0, 0, 1},    // 68 MiB
       {64, (int64_t(1) << 19) - 32, 1, 0, 0, 1}, {64, int64_t(1) << 19, 1, 0, 0, 2},  // 128 MiB
-      {24, int64_t(1) << 21, 1, 0, 0, 1}, {24, 100 << 14, 1, 0, 0, 1},
-      {32, 100 << 14, 1, 0, 0, 2}, {25, int64_t(1) << 21, 1, 0, 0, 2},  // 200 MiB below 33 ranks
-      {24, (3 << 19) - 32, 2, 0, 4, 1}, {24, 3 << 20, 1, 0, 4, 2},  // off the lines 288 MiB
+      {64, (int64_t(1) << 19) - 32, 1, 0, 4, 1}, {64, int64_t(1) << 19, 1, 0, 4, 2},
+      {24, 3 << 19, 1, 0, 0, 2}, {24, (3 << 19) - 32, 1, 0, 0, 1}, {24, 3 << 19, 1, 0, 4, 2},  // 144 MiB below 33 ranks
+      {24, (3 << 18) - 32, 2, 0, 0, 1}, {24, 3 << 18, 2, 0, 0, 2},
       {37, 106, 65536, 0, 0, 2}, {64, 106, 65536, 0, 0, 2}, {127, 106, 65536, 0, 0, 2},
       {127, 106, 2400, 0, 0, 1}, {127, 106, 2550, 0, 0, 2},
       {127, 2304, 8192, 0, 0, 2},

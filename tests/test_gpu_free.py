@@ -49,9 +49,10 @@ def launches(P, n, B, pitch, k):
 @pytest.mark.parametrize("P,k", [(16, 4), (17, 5), (24, 10), (100, 14)])
 def test_split_by_size_and_one_launch_agree(P, k):
     """Calls just below and at the size from which int32 plans of 17 ranks and
-    more split, rows off the lines (288 MiB over all ranks): one instance, and
-    a batch of short ones, whose size is that of all its instances."""
-    least = (288 << 20) // 4 // P
+    more split, rows off the lines (144 MiB over all ranks, 128 MiB from 33
+    ranks): one instance, and a batch of short ones, whose size is that of all
+    its instances."""
+    least = ((144 if P < 33 else 128) << 20) // 4 // P
     for n, B in ((least - 1, 1), (least, 1), (106, least // 106), (106, least // 106 + 1)):
         want = 2 if P >= 17 and n * B >= least else 1
         note("int32 split P=%d n=%d B=%d k=%d" % (P, n, B, k))
@@ -60,7 +61,7 @@ def test_split_by_size_and_one_launch_agree(P, k):
             check(P, n, k, B=B, lead=1, dtype="int32", op="max")
 
 
-@pytest.mark.parametrize("P,mib", [(24, 200), (33, 128), (127, 128)])
+@pytest.mark.parametrize("P,mib", [(24, 144), (33, 128), (127, 128)])
 def test_split_size_on_the_lines(P, mib):
     least = (mib << 20) // 4 // P
     for n, B in ((least - 1, 1), (least, 1), (106, least // 106), (106, least // 106 + 1)):
